@@ -158,6 +158,38 @@ int bf1_dense_causal_fwd(const void* Q, const void* K, const void* V, void* O, f
                          void* stream);
 
 /*
+ * Pieces of the whole-model prefill (§4.3, §5.3), used by the decoder stack of
+ * the Python package around the library GEMMs.  Activations and gains are
+ * bf16, rotary tables fp32, all pointers 16-byte aligned device memory;
+ * arithmetic is fp32, rounded to bf16 after each operator named below.
+ *
+ * bf1_attn_fwd_token_major: bf1_attn_fwd (dense = 0) or bf1_dense_causal_fwd
+ *   (dense = 1; B and L ignored) with O as [batch, n, Hq, head_dim], the
+ *   layout the output projection reads; no LSE.  Same kernels, the same bits.
+ * bf1_stack_rms: out = RMSNorm(h) * gain over rows of `cols` elements; with r
+ *   given, h <- h + r first (h is updated in place).  cols a multiple of 8 and
+ *   at most 4096, others BF1_ERR_UNSUPPORTED.
+ * bf1_stack_heads: projections q [n, H head_dim] and k, v [n, Hkv head_dim]
+ *   (row strides ldq, ldk, ldv in elements, multiples of 8) to head-major
+ *   Q [H, n, head_dim] and K, V [Hkv, n, head_dim]; every Q and K row gets
+ *   RMSNorm with qgain / kgain [head_dim] and then the rotary embedding of
+ *   its position (cosv, sinv [n, head_dim], both halves of a row equal).
+ *   head_dim in {64, 128}.
+ * bf1_stack_swiglu: out = silu(g) * u, [rows, cols] with row strides ldg, ldu
+ *   (multiples of 8), out contiguous; cols a multiple of 8.
+ */
+int bf1_attn_fwd_token_major(const void* Q, const void* K, const void* V, void* O, int32_t batch, int64_t n,
+                             int32_t Hq, int32_t Hkv, int32_t head_dim, int32_t B, int32_t L, int32_t dense,
+                             void* stream);
+int bf1_stack_rms(void* h, const void* r, const void* gain, void* out, int64_t rows, int32_t cols, float eps,
+                  void* stream);
+int bf1_stack_heads(const void* q, const void* k, const void* v, int64_t ldq, int64_t ldk, int64_t ldv,
+                    const void* qgain, const void* kgain, const float* cosv, const float* sinv, void* Q, void* K,
+                    void* V, int64_t n, int32_t H, int32_t Hkv, int32_t head_dim, float eps, void* stream);
+int bf1_stack_swiglu(const void* g, const void* u, int64_t ldg, int64_t ldu, void* out, int64_t rows, int32_t cols,
+                     void* stream);
+
+/*
  * Transposed route (host only, no device work): for every key block i the
  * ascending query blocks j whose route P(j) (§3.1, Eq. 1) contains i -- all
  * blocks for i = 0 (the global block), otherwise i, its L local successors

@@ -73,6 +73,16 @@ def load():
     lib.bf1_attn_fwd_csr.argtypes = attn + [i32, vp, vp, i64, vp]
     lib.bf1_dense_causal_fwd.restype = ctypes.c_int
     lib.bf1_dense_causal_fwd.argtypes = attn + [vp]
+    f32 = ctypes.c_float
+    lib.bf1_attn_fwd_token_major.restype = ctypes.c_int
+    lib.bf1_attn_fwd_token_major.argtypes = [vp, vp, vp, vp, i32, i64, i32, i32, i32, i32, i32, i32, vp]
+    lib.bf1_stack_rms.restype = ctypes.c_int
+    lib.bf1_stack_rms.argtypes = [vp, vp, vp, vp, i64, i32, f32, vp]
+    lib.bf1_stack_heads.restype = ctypes.c_int
+    lib.bf1_stack_heads.argtypes = [vp, vp, vp, i64, i64, i64, vp, vp, vp, vp, vp, vp, vp, i64, i32, i32, i32, f32,
+                                    vp]
+    lib.bf1_stack_swiglu.restype = ctypes.c_int
+    lib.bf1_stack_swiglu.argtypes = [vp, vp, i64, i64, vp, i64, i32, vp]
     lib.bf1_set_forward_key_split.restype = ctypes.c_int
     lib.bf1_set_forward_key_split.argtypes = [i32]
     lib.bf1_release_plans.restype = None

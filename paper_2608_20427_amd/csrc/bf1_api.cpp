@@ -393,6 +393,27 @@ int bf1_dense_causal_fwd(const void* Q, const void* K, const void* V, void* O, f
     return run_attn(a, (hipStream_t)stream);
 }
 
+int bf1_attn_fwd_token_major(const void* Q, const void* K, const void* V, void* O, int32_t batch, int64_t n,
+                             int32_t Hq, int32_t Hkv, int32_t head_dim, int32_t B, int32_t L, int32_t dense,
+                             void* stream) {
+    int st = check_attn(Q, K, V, O, nullptr, batch, n, Hq, Hkv, head_dim);
+    if (st != BF1_OK) return st;
+    if (dense != 0 && dense != 1) return BF1_ERR_INVALID_ARG;
+    if (!dense && L < 0) return BF1_ERR_INVALID_ARG;
+    if (!dense && B != 64 && B != 128) return BF1_ERR_UNSUPPORTED;
+    if (batch == 0 || n == 0) return BF1_OK;
+    hipStream_t s = (hipStream_t)stream;
+    Plan plan;
+    if (!dense) {
+        st = get_plan(n, B, L, s, &plan);
+        if (st != BF1_OK) return st;
+    }
+    bf1::AttnArgs a{Q, K, V, O, nullptr, plan.row_ptr, plan.col_idx, plan.nnz,
+                    batch, n, Hq, Hkv, head_dim, dense ? 64 : B, dense == 1};
+    a.token_major = true;
+    return run_attn(a, s);
+}
+
 int bf1_plan_transposed(int64_t n, int32_t B, int32_t L, int32_t* row_ptr, int32_t* col_idx,
                         int64_t col_capacity) {
     if (n < 0 || B < 1 || L < 0 || col_capacity < 0 || !row_ptr) return BF1_ERR_INVALID_ARG;

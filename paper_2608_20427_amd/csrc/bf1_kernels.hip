@@ -153,12 +153,30 @@ __device__ __forceinline__ void lds_read_tr16_x8(uint32_t addr, u32x2 (&v)[8]) {
 // and unnormalised rows to group 0 through LDS, which merges and stores.  An
 // item's chain of key tiles is halved, and two waves share each SIMD where a
 // single workgroup would otherwise leave one.
+//
+// Where the results go is the kernel's first argument and is read from the
+// argument segment only in the epilogue, through a pointer the compiler cannot
+// see through: held from the start it costs scalar registers for the whole
+// loop, which is out of them (100 in use, the rest spilled to vector lanes).
+struct OutArgs {
+    __bf16* O;
+    float* LSE;      // may be null
+    int32_t o_tok;   // rows of O (D elements) from one token to the next ...
+    int32_t o_head;  // ... and from one head to the next
+};
+__device__ __forceinline__ OutArgs out_args() {
+    typedef const __attribute__((address_space(4))) OutArgs* arg_ptr;
+    uint64_t p = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    const arg_ptr a = (arg_ptr)p;
+    return OutArgs{a->O, a->LSE, a->o_tok, a->o_head};
+}
+
 template <int D, int G, int BW, int NW, bool DENSE, int KSPLIT>
 __global__ __launch_bounds__(NW * 64 * KSPLIT, KSPLIT == 1 ? 2 : 1) void attn_fwd_kernel(
-    const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
-    __bf16* __restrict__ O, float* __restrict__ LSE, const int32_t* __restrict__ row_ptr,
-    const int32_t* __restrict__ col_idx, int64_t nnz, int32_t n, int32_t NB, int32_t batch_hkv,
-    int32_t Hkv, float c_log2) {
+    OutArgs, const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
+    const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int64_t nnz, int32_t n,
+    int32_t NB, int32_t batch_hkv, int32_t Hkv, float c_log2) {
     constexpr int ROWS = NW * 32;             // stacked query rows per workgroup
     constexpr int NCHUNK = (G * BW + ROWS - 1) / ROWS;
     constexpr int NSUB = BW / KT;             // LDS tiles per key block
@@ -370,12 +388,13 @@ __global__ __launch_bounds__(NW * 64 * KSPLIT, KSPLIT == 1 ? 2 : 1) void attn_fw
         // A row with no usable key block (possible only for a caller route
         // table): O = 0, LSE = -inf.
         if (qvalid && grp == 0) {
-            __bf16* Orow = O + (((int64_t)beta * Hq + head) * (int64_t)n + qpos) * D;
+            const OutArgs oa = out_args();
+            __bf16* Orow = oa.O + ((int64_t)beta * Hq * n + (int64_t)head * oa.o_head + (int64_t)qpos * oa.o_tok) * D;
 #pragma unroll
             for (int c = 0; c < D / 2; c += 8)
                 *reinterpret_cast<u32x4*>(Orow + half * (D / 2) + c) = u32x4{0u, 0u, 0u, 0u};
-            if (LSE != nullptr && half == 0)
-                LSE[((int64_t)beta * Hq + head) * (int64_t)n + qpos] = -INFINITY;
+            if (oa.LSE != nullptr && half == 0)
+                oa.LSE[((int64_t)beta * Hq + head) * (int64_t)n + qpos] = -INFINITY;
         }
         return;
     }
@@ -638,20 +657,25 @@ __global__ __launch_bounds__(NW * 64 * KSPLIT, KSPLIT == 1 ? 2 : 1) void attn_fw
             *reinterpret_cast<bf16x4*>(oslice + col * RB + ch * 16 + half * 8) =
                 __builtin_convertvector(v4, bf16x4);
         }
+    const OutArgs oa = out_args();
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's O tile is in LDS
     {
         const int32_t row0 = j * BW + p0;  // first query of this wave
-        __bf16* Obase = O + (((int64_t)beta * Hq + head) * (int64_t)n + row0) * D;
+        __bf16* Obase = oa.O + ((int64_t)beta * Hq * n + (int64_t)head * oa.o_head + (int64_t)row0 * oa.o_tok) * D;
+        const int64_t ostep = (int64_t)oa.o_tok * D;  // elements from one token's row to the next
         constexpr int RPI = 64 / OCH;      // rows per store instruction
+        const int c = lane % OCH;
+        __bf16* dst = Obase + (lane / OCH) * ostep + c * 8;
 #pragma unroll
         for (int it = 0; it < 32 / RPI; ++it) {
-            const int r = it * RPI + lane / OCH, c = lane % OCH;
+            const int r = it * RPI + lane / OCH;
             const u32x4 w = *reinterpret_cast<const u32x4*>(oslice + r * RB + ((c ^ (r % OCH)) * 16));
-            if (row0 + r < n) __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(Obase + (int64_t)r * D + c * 8));
+            if (row0 + r < n) __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(dst));
+            dst += RPI * ostep;
         }
     }
-    if (LSE != nullptr && half == 0 && qvalid)
-        LSE[((int64_t)beta * Hq + head) * (int64_t)n + qpos] = (m_run + log2f(l_tot)) * LN2;
+    if (oa.LSE != nullptr && half == 0 && qvalid)
+        oa.LSE[((int64_t)beta * Hq + head) * (int64_t)n + qpos] = (m_run + log2f(l_tot)) * LN2;
 }
 
 // Two key groups per workgroup: never (mode 1), always (mode 2), or (mode 0,
@@ -692,20 +716,21 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t stream) {
     if (items == 0) return hipSuccess;
     if (items > 0x7fffffff) return hipErrorInvalidValue;
     const float c_log2 = (1.0f / sqrtf((float)D)) * LOG2E;
+    const OutArgs out{(__bf16*)a.O, a.LSE, a.token_major ? a.Hq : 1, a.token_major ? 1 : (int32_t)a.n};
     // key tiles the launch walks (the dense route {0..j} has NB (NB + 1) / 2
     // blocks per kv-head; a caller table is taken at its size)
     const int64_t blocks = DENSE ? (int64_t)NB * (NB + 1) / 2 : a.nnz;
     const int64_t tiles = blocks * (BW / KT) * a.batch * a.Hkv * NCHUNK;
     if (use_key_split(a.key_split, items, tiles)) {
         hipLaunchKernelGGL((attn_fwd_kernel<D, G, BW, NW, DENSE, 2>), dim3((unsigned)items),
-                           dim3(2 * NW * 64), 0, stream, (const __bf16*)a.Q, (const __bf16*)a.K,
-                           (const __bf16*)a.V, (__bf16*)a.O, a.LSE, a.row_ptr, a.col_idx, a.nnz,
-                           (int32_t)a.n, NB, a.batch * a.Hkv, a.Hkv, c_log2);
+                           dim3(2 * NW * 64), 0, stream, out, (const __bf16*)a.Q, (const __bf16*)a.K,
+                           (const __bf16*)a.V, a.row_ptr, a.col_idx, a.nnz, (int32_t)a.n, NB,
+                           a.batch * a.Hkv, a.Hkv, c_log2);
     } else {
         hipLaunchKernelGGL((attn_fwd_kernel<D, G, BW, NW, DENSE, 1>), dim3((unsigned)items),
-                           dim3(NW * 64), 0, stream, (const __bf16*)a.Q, (const __bf16*)a.K,
-                           (const __bf16*)a.V, (__bf16*)a.O, a.LSE, a.row_ptr, a.col_idx, a.nnz,
-                           (int32_t)a.n, NB, a.batch * a.Hkv, a.Hkv, c_log2);
+                           dim3(NW * 64), 0, stream, out, (const __bf16*)a.Q, (const __bf16*)a.K,
+                           (const __bf16*)a.V, a.row_ptr, a.col_idx, a.nnz, (int32_t)a.n, NB,
+                           a.batch * a.Hkv, a.Hkv, c_log2);
     }
     return hipGetLastError();
 }

@@ -4,17 +4,20 @@ A decoder stack of the evaluated geometry (Qwen3-0.6B: 28 layers, 16 query
 heads, 8 kv-heads, head dimension 128, §4.1) whose attention layers run this
 library's kernels: bf1_attn_fwd on the BF1 route for the chosen layers, the
 in-house dense causal kernel (bf1_dense_causal_fwd) for the others.  The
-projections, norms, rotary embedding and MLP around them are plain PyTorch
-operators on the GPU (hipBLASLt GEMMs and eager elementwise kernels), as in
-the paper's eager harness; the study measures the time to first token (the
+projections around them are library GEMMs; the norms with their residual adds,
+the per-head norm with the rotary embedding and the SwiGLU product between
+them are one HIP kernel each (plain PyTorch operators with the same rounding
+where those kernels do not apply).  The study measures the time to first token (the
 last position's logits) with no, the middle eight, or all layers on the BF1
 route.  The trained weights are not available: callers pass seeded random
 weights of the published shapes (timing does not depend on their values).
 """
 
+import contextlib
+
 import torch
 
-from . import attn_fwd, dense_causal_fwd
+from . import _check, _ptr, _stream, attn_fwd, dense_causal_fwd, load
 
 __all__ = ["middle_layers", "PrefillStack"]
 
@@ -58,34 +61,111 @@ class PrefillStack:
         rot = torch.cat([-xf[..., half:], xf[..., :half]], dim=-1)
         return (xf * cos + rot * sin).to(torch.bfloat16)
 
+    # ---- one layer ------------------------------------------------------------
+
+    def _attention(self, l, Q, K, V, bf1_layers, dense_attention):
+        if l in bf1_layers:
+            return attn_fwd(Q, K, V, self.B, self.L, want_lse=False)[0]
+        if dense_attention is not None:
+            return dense_attention(Q, K, V)
+        return dense_causal_fwd(Q, K, V, want_lse=False)[0]
+
+    def _layer_plain(self, l, h, cos, sin, bf1_layers, dense_attention):
+        """One layer, operator by operator: any device, type and shape."""
+        cfg, w, p = self.cfg, self.w, f"{l}."
+        n, H, Hkv, d = h.shape[0], cfg.heads, cfg.kv_heads, cfg.head_dim
+        a = self._rms(h, w[p + "in_norm"])
+        q = self._rms((a @ w[p + "wq"]).view(n, H, d), w[p + "q_norm"])
+        k = self._rms((a @ w[p + "wk"]).view(n, Hkv, d), w[p + "k_norm"])
+        v = (a @ w[p + "wv"]).view(n, Hkv, d)
+        q, k = self._rope(q, cos, sin), self._rope(k, cos, sin)
+        Q = q.transpose(0, 1).contiguous().unsqueeze(0)
+        K = k.transpose(0, 1).contiguous().unsqueeze(0)
+        V = v.transpose(0, 1).contiguous().unsqueeze(0)
+        O = self._attention(l, Q, K, V, bf1_layers, dense_attention)
+        h = h + O[0].transpose(0, 1).reshape(n, H * d) @ w[p + "wo"]
+        a = self._rms(h, w[p + "post_norm"])
+        return h + (torch.nn.functional.silu(a @ w[p + "wg"]) * (a @ w[p + "wu"])) @ w[p + "wd"]
+
+    def _fused(self, l, h, cos):
+        """Whether layer l can run on the row kernels: bf16 weights of matching
+        shapes on h's GPU, the kernels' head sizes and widths, and no autograd
+        graph wanted through the layer."""
+        cfg, w, p = self.cfg, self.w, f"{l}."
+        if type(h) is not torch.Tensor or not h.is_cuda or h.dtype != torch.bfloat16 or h.dim() != 2 \
+                or cos.device != h.device:
+            return False
+        n, hidden = h.shape
+        H, Hkv, d = cfg.heads, cfg.kv_heads, cfg.head_dim
+        if n == 0 or d not in (64, 128) or hidden % 8 or hidden > 4096 or max(H, Hkv) > 4096:
+            return False
+        inter = w[p + "wg"].shape[-1]
+        if inter % 8:
+            return False
+        grad = torch.is_grad_enabled()
+        if grad and h.requires_grad:
+            return False
+        dev = h.device
+        for name, shape in (("in_norm", (hidden,)), ("q_norm", (d,)), ("k_norm", (d,)), ("post_norm", (hidden,)),
+                            ("wq", (hidden, H * d)), ("wk", (hidden, Hkv * d)), ("wv", (hidden, Hkv * d)),
+                            ("wo", (H * d, hidden)), ("wg", (hidden, inter)), ("wu", (hidden, inter)),
+                            ("wd", (inter, hidden))):
+            t = w[p + name]
+            if t.shape != shape or t.dtype != torch.bfloat16 or t.device != dev or (grad and t.requires_grad):
+                return False
+            if len(shape) == 1 and (not t.is_contiguous() or t.data_ptr() % 16):
+                return False
+        return True
+
+    def _rms_fused(self, h, r, gain):
+        """h <- h + r in place (if r is given), then RMSNorm(h) * gain."""
+        out = torch.empty_like(h)
+        _check(load().bf1_stack_rms(_ptr(h), _ptr(r), _ptr(gain), _ptr(out), h.shape[0], h.shape[1], self.cfg.eps,
+                                    _stream(None)), "bf1_stack_rms")
+        return out
+
+    def _layer_fused(self, l, h, r, cos, sin, bf1_layers, dense_attention):
+        """One layer between library GEMMs on the row kernels; h is updated in
+        place.  r is the previous layer's MLP output (None before the first),
+        not yet added to h; returns this layer's."""
+        cfg, w, p, lib = self.cfg, self.w, f"{l}.", load()
+        n, H, Hkv, d = h.shape[0], cfg.heads, cfg.kv_heads, cfg.head_dim
+        a = self._rms_fused(h, r, w[p + "in_norm"])
+        q, k, v = a @ w[p + "wq"], a @ w[p + "wk"], a @ w[p + "wv"]
+        Q, K, V = (torch.empty((1, x, n, d), dtype=h.dtype, device=h.device) for x in (H, Hkv, Hkv))
+        _check(lib.bf1_stack_heads(_ptr(q), _ptr(k), _ptr(v), q.stride(0), k.stride(0), v.stride(0),
+                                   _ptr(w[p + "q_norm"]), _ptr(w[p + "k_norm"]), _ptr(cos), _ptr(sin), _ptr(Q),
+                                   _ptr(K), _ptr(V), n, H, Hkv, d, cfg.eps, _stream(None)), "bf1_stack_heads")
+        if l not in bf1_layers and dense_attention is not None:
+            O = dense_attention(Q, K, V)[0].transpose(0, 1).reshape(n, H * d)
+        else:
+            O = torch.empty((n, H * d), dtype=h.dtype, device=h.device)
+            _check(lib.bf1_attn_fwd_token_major(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), 1, n, H, Hkv, d, int(self.B),
+                                                int(self.L), int(l not in bf1_layers), _stream(None)),
+                   "bf1_attn_fwd_token_major")
+        a = self._rms_fused(h, O @ w[p + "wo"], w[p + "post_norm"])
+        g, u = a @ w[p + "wg"], a @ w[p + "wu"]
+        s = torch.empty_like(g)
+        _check(lib.bf1_stack_swiglu(_ptr(g), _ptr(u), g.stride(0), u.stride(0), _ptr(s), n, g.shape[1],
+                                    _stream(None)), "bf1_stack_swiglu")
+        return s @ w[p + "wd"]
+
     def last_logits(self, ids, bf1_layers, dense_attention=None):
         """Logits (float32, [vocab]) of the last position after the prefill of
         token ids (int64 device tensor [n]).  dense_attention, if given,
         replaces the in-house dense kernel for the non-BF1 layers: a callable
         (Q, K, V) -> O on [1, heads, n, d] bf16 tensors (a comparator)."""
         cfg, w = self.cfg, self.w
-        n = ids.shape[0]
-        H, Hkv, d = cfg.heads, cfg.kv_heads, cfg.head_dim
-        cos, sin = self._rope_tables(n)
+        cos, sin = self._rope_tables(ids.shape[0])
         h = w["embed"][ids]
-        for l in range(cfg.layers):
-            p = f"{l}."
-            a = self._rms(h, w[p + "in_norm"])
-            q = self._rms((a @ w[p + "wq"]).view(n, H, d), w[p + "q_norm"])
-            k = self._rms((a @ w[p + "wk"]).view(n, Hkv, d), w[p + "k_norm"])
-            v = (a @ w[p + "wv"]).view(n, Hkv, d)
-            q, k = self._rope(q, cos, sin), self._rope(k, cos, sin)
-            Q = q.transpose(0, 1).contiguous().unsqueeze(0)
-            K = k.transpose(0, 1).contiguous().unsqueeze(0)
-            V = v.transpose(0, 1).contiguous().unsqueeze(0)
-            if l in bf1_layers:
-                O, _ = attn_fwd(Q, K, V, self.B, self.L, want_lse=False)
-            elif dense_attention is not None:
-                O = dense_attention(Q, K, V)
-            else:
-                O, _ = dense_causal_fwd(Q, K, V, want_lse=False)
-            h = h + O[0].transpose(0, 1).reshape(n, H * d) @ w[p + "wo"]
-            a = self._rms(h, w[p + "post_norm"])
-            h = h + (torch.nn.functional.silu(a @ w[p + "wg"]) * (a @ w[p + "wu"])) @ w[p + "wd"]
-        last = self._rms(h[-1:], w["final_norm"])
+        r = None  # MLP output of the layer before, not yet added to h
+        with torch.cuda.device(h.device) if h.is_cuda else contextlib.nullcontext():
+            for l in range(cfg.layers):
+                if self._fused(l, h, cos):
+                    r = self._layer_fused(l, h, r, cos, sin, bf1_layers, dense_attention)
+                    continue
+                h, r = h if r is None else h + r, None
+                h = self._layer_plain(l, h, cos, sin, bf1_layers, dense_attention)
+        last = h[-1:] if r is None else h[-1:] + r[-1:]
+        last = self._rms(last, w["final_norm"])
         return (last @ w["embed"].t()).float()[0]

@@ -1,0 +1,176 @@
+"""GPU checks of the prefill stack's row kernels: RMSNorm with the residual
+add, head split with per-head norm and rotary embedding, SwiGLU, and the
+token-major attention output.
+
+Bars, from the arithmetic: every kernel computes in fp32 (a handful of
+roundings of 2^-24 each, the mean over up to 4096 terms another 2^-20) and
+rounds to bf16 (8 significant bits: at most half an ulp, 2^-8 relative) where
+the operator sequence rounds.  One rounding: |err| <= (2^-8 + 2^-16) |y|.  Two
+roundings, the first scaled by the second factor (norm then rotation, silu then
+product): 2^-7 plus
+the same slack, of the magnitudes that are added.
+"""
+
+import ctypes
+
+import pytest
+import torch
+
+import paper_2608_20427_amd as bf1
+from paper_2608_20427_amd import synth
+from paper_2608_20427_amd.prefill_model import PrefillStack
+
+pytestmark = pytest.mark.gpu
+EPS = 1e-6
+
+
+def _n(g, *shape, mul=1.0):
+    return (mul * torch.randn(shape, generator=g, device="cuda")).to(torch.bfloat16)
+
+
+def _g(seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return g
+
+
+def _call(name, *args):
+    conv = [ctypes.c_void_p(a.data_ptr()) if isinstance(a, torch.Tensor) else a for a in args]
+    st = getattr(bf1.load(), name)(*conv, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    return st
+
+
+@pytest.mark.parametrize("residual", [False, True])
+@pytest.mark.parametrize("rows,cols", [(1, 8), (3, 504), (4, 512), (5, 1024), (6, 1032), (9, 2048), (2, 2056),
+                                       (7, 4096)])
+def test_rms(rows, cols, residual):
+    print("rms", rows, cols, residual, flush=True)
+    g = _g(rows * 10000 + cols)
+    h, r, w = _n(g, rows, cols, mul=3), _n(g, rows, cols), _n(g, cols)
+    want_h = (h + r) if residual else h.clone()
+    x = want_h.double()
+    ref = x * torch.rsqrt(x.pow(2).mean(-1, keepdim=True) + EPS) * w.double()
+    out = torch.empty_like(h)
+    assert _call("bf1_stack_rms", h, r if residual else None, w, out, rows, cols, EPS) == bf1.BF1_OK
+    assert torch.equal(h, want_h)
+    assert ((out.double() - ref).abs() <= (2.0 ** -8 + 2.0 ** -16) * ref.abs()).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n,H,Hkv,pad", [(1, 1, 1, 0), (7, 4, 2, 0), (129, 3, 1, 8), (64, 16, 8, 0)])
+def test_heads(d, n, H, Hkv, pad):
+    print("heads", d, n, H, Hkv, pad, flush=True)
+    g = _g(d + n + H)
+    q, k, v = (_n(g, n, x * d + pad, mul=2) for x in (H, Hkv, Hkv))
+    wq, wk = _n(g, d), _n(g, d)
+    ang = torch.arange(n, dtype=torch.float64, device="cuda")[:, None] * \
+        1e6 ** (-torch.arange(0, d, 2, dtype=torch.float64, device="cuda") / d)[None]
+    cos, sin = (torch.cat([f, f], -1).float().contiguous() for f in (ang.cos(), ang.sin()))
+    Q, K, V = (torch.empty((x, n, d), dtype=torch.bfloat16, device="cuda") for x in (H, Hkv, Hkv))
+    assert _call("bf1_stack_heads", q, k, v, q.stride(0), k.stride(0), v.stride(0), wq, wk, cos, sin, Q, K, V, n, H,
+                 Hkv, d, EPS) == bf1.BF1_OK
+    assert torch.equal(V, v[:, :Hkv * d].view(n, Hkv, d).transpose(0, 1))
+    for got, src, w, heads in ((Q, q, wq, H), (K, k, wk, Hkv)):
+        x = src[:, :heads * d].reshape(n, heads, d).double()
+        x = x * torch.rsqrt(x.pow(2).mean(-1, keepdim=True) + EPS) * w.double()
+        a, b = x[..., :d // 2], x[..., d // 2:]
+        c, s = cos.double()[:, None, :d // 2], sin.double()[:, None, :d // 2]
+        ref = torch.cat([a * c - b * s, b * c + a * s], -1).transpose(0, 1)
+        mag = torch.cat([(a * c).abs() + (b * s).abs(), (b * c).abs() + (a * s).abs()], -1).transpose(0, 1)
+        assert ((got.double() - ref).abs() <= (2.0 ** -7 + 2.0 ** -14) * mag).all()
+
+
+@pytest.mark.parametrize("rows,cols,pad", [(1, 8, 0), (3, 40, 8), (257, 3072, 0)])
+def test_swiglu(rows, cols, pad):
+    print("swiglu", rows, cols, pad, flush=True)
+    g = _g(rows + cols)
+    a, u = _n(g, rows, cols + pad, mul=8), _n(g, rows, cols + pad)
+    a[0, 0], a[0, 1] = -100.0, 100.0      # exp overflows to infinity and to zero
+    out = torch.empty((rows, cols), dtype=torch.bfloat16, device="cuda")
+    assert _call("bf1_stack_swiglu", a, u, a.stride(0), u.stride(0), out, rows, cols) == bf1.BF1_OK
+    x = a[:, :cols].double()
+    ref = x * torch.sigmoid(x) * u[:, :cols].double()
+    # results below fp32's smallest normal number may be flushed
+    assert ((out.double() - ref).abs() <= (2.0 ** -7 + 2.0 ** -14) * ref.abs() + 1e-36).all()
+
+
+@pytest.mark.parametrize("cfg", [(1, 64, 2, 1, 64, 64), (2, 129, 4, 2, 128, 64), (1, 700, 8, 1, 64, 128),
+                                 (2, 300, 2, 2, 128, 128)])
+@pytest.mark.parametrize("dense", [0, 1])
+@pytest.mark.parametrize("split", [1, 2])
+def test_token_major_output_is_bitwise_the_forward(cfg, dense, split):
+    batch, n, Hq, Hkv, d, B = cfg
+    print("token major", cfg, dense, split, flush=True)
+    g = _g(n)
+    q, k, v = _n(g, batch, Hq, n, d), _n(g, batch, Hkv, n, d), _n(g, batch, Hkv, n, d)
+    out = torch.full((batch, n, Hq, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    bf1.set_forward_key_split(split)
+    try:
+        ref, _ = bf1.dense_causal_fwd(q, k, v) if dense else bf1.attn_fwd(q, k, v, B, 2)
+        assert _call("bf1_attn_fwd_token_major", q, k, v, out, batch, n, Hq, Hkv, d, B, 2, dense) == bf1.BF1_OK
+    finally:
+        bf1.set_forward_key_split(0)
+    assert torch.equal(out.transpose(1, 2), ref)
+
+
+def test_arguments_rejected():
+    t = torch.zeros(8192, dtype=torch.bfloat16, device="cuda")
+    f = torch.zeros(128, device="cuda")
+    odd = ctypes.c_void_p(t.data_ptr() + 2)
+    assert _call("bf1_stack_rms", t, None, t, t, 1, 12, EPS) == bf1.BF1_ERR_UNSUPPORTED
+    assert _call("bf1_stack_rms", t, None, t, t, 1, 4104, EPS) == bf1.BF1_ERR_UNSUPPORTED
+    assert _call("bf1_stack_rms", odd, None, t, t, 1, 8, EPS) == bf1.BF1_ERR_INVALID_ARG
+    assert _call("bf1_stack_swiglu", t, t, 4, 8, t, 1, 8) == bf1.BF1_ERR_INVALID_ARG
+    assert _call("bf1_stack_swiglu", t, t, 12, 12, t, 1, 12) == bf1.BF1_ERR_UNSUPPORTED
+    assert _call("bf1_stack_heads", t, t, t, 96, 96, 96, t, t, f, f, t, t, t, 1, 1, 1, 96, EPS) == \
+        bf1.BF1_ERR_UNSUPPORTED
+    assert _call("bf1_attn_fwd_token_major", t, t, t, t, 1, 8, 1, 1, 64, 96, 2, 0) == bf1.BF1_ERR_UNSUPPORTED
+    assert _call("bf1_attn_fwd_token_major", t, t, t, t, 1, 8, 1, 1, 64, 64, 2, 2) == bf1.BF1_ERR_INVALID_ARG
+
+
+CFG = synth.ModelConfig(layers=3, hidden=256, heads=4, kv_heads=2, head_dim=64, intermediate=512, vocab=1000)
+
+
+def _stack(cfg=CFG, **replace):
+    st = PrefillStack(cfg, synth.make_model_weights(cfg, 11), device="cuda")
+    st.w.update({k: f(st.w[k]) for k, f in replace.items()})
+    return st
+
+
+def test_fused_stack_matches_the_operators_and_mixes_with_them():
+    # the two forms round at the same places, so a few bf16 ulps of the largest
+    # logit separate them; a layer the kernels do not take (a float32 norm gain
+    # here) runs operator by operator between fused ones
+    ids = torch.from_numpy(synth.make_tokens(CFG, 333, 4)).cuda()
+    st = _stack()
+    plain = _stack()
+    plain._fused = lambda *a: False
+    mixed = _stack(**{"1.in_norm": lambda t: t.float()})
+    cos, _ = mixed._rope_tables(333)
+    h = mixed.w["embed"][ids]
+    assert [mixed._fused(l, h, cos) for l in range(3)] == [True, False, True]
+    for layers in (set(), {0, 2}, {0, 1, 2}):
+        a, b, c = (s.last_logits(ids, layers) for s in (st, plain, mixed))
+        top = b.abs().max()
+        assert (a - b).abs().max() <= 2e-2 * top and (c - b).abs().max() <= 2e-2 * top
+
+
+def test_autograd_keeps_the_operators():
+    st = _stack(**{"2.wd": lambda t: t.clone().requires_grad_()})
+    ids = torch.from_numpy(synth.make_tokens(CFG, 70, 4)).cuda()
+    st.last_logits(ids, {0}).sum().backward()
+    assert st.w["2.wd"].grad is not None and torch.isfinite(st.w["2.wd"].grad).all()
+
+
+def test_dense_attention_callable_sees_contiguous_heads():
+    st = _stack()
+    ids = torch.from_numpy(synth.make_tokens(CFG, 200, 4)).cuda()
+    seen = []
+
+    def dense(Q, K, V):
+        seen.append((tuple(Q.shape), tuple(K.shape), Q.is_contiguous() and K.is_contiguous() and V.is_contiguous()))
+        return bf1.dense_causal_fwd(Q, K, V, want_lse=False)[0]
+    a = st.last_logits(ids, {1}, dense)
+    assert seen == [((1, 4, 200, 64), (1, 2, 200, 64), True)] * 2
+    assert torch.equal(a, st.last_logits(ids, {1}))
