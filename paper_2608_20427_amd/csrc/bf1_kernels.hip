@@ -272,14 +272,21 @@ __global__ __launch_bounds__(NW * 64 * KSPLIT, KSPLIT == 1 ? 2 : 1) void attn_fw
         }
         while (cur_p < pos_end) {
             const int32_t i = pref;
-            if (i >= 0 && i <= j) {
-                for (; cur_u < NSUB; ++cur_u)
-                    if (i * BW + cur_u * KT < n) {
-                        ti = i;
-                        tu = cur_u++;
-                        if (cur_u >= NSUB) advance();
-                        return true;
-                    }
+            // Written without a loop over the sub-tiles: with one the compiler
+            // unrolls the search (64K tokens at block width 128: 780 us with the
+            // loop, 765 us without; at width 64 there is nothing to search).
+            if constexpr (NSUB == 1) {  // a block up to j starts before n
+                if (i >= 0 && i <= j) {
+                    ti = i;
+                    tu = 0;
+                    advance();
+                    return true;
+                }
+            } else if ((uint32_t)i <= (uint32_t)j && i * BW + cur_u * KT < n) {
+                ti = i;
+                tu = cur_u;
+                if (++cur_u >= NSUB) advance();
+                return true;
             }
             advance();
         }
