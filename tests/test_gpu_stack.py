@@ -174,3 +174,26 @@ def test_dense_attention_callable_sees_contiguous_heads():
     a = st.last_logits(ids, {1}, dense)
     assert seen == [((1, 4, 200, 64), (1, 2, 200, 64), True)] * 2
     assert torch.equal(a, st.last_logits(ids, {1}))
+
+
+def test_joined_projections_follow_w():
+    # the joined matrices are only a layout of w: an update in place is seen,
+    # a replaced entry is used as it is, and the values are those given
+    ids = torch.from_numpy(synth.make_tokens(CFG, 90, 4)).cuda()
+    given = synth.make_model_weights(CFG, 11)
+    st = _stack()
+    assert all(torch.equal(st.w[k].cpu(), given[k]) for k in given)
+    base = st.last_logits(ids, {0})
+    st.w["1.wk"].mul_(2)          # in place, inside the joined matrix
+    twice = st.last_logits(ids, {0})
+    other = _stack(**{"1.wk": lambda t: (t * 2).contiguous()})  # its own matrix now
+    a = torch.zeros((4, CFG.hidden), dtype=torch.bfloat16, device="cuda")
+    assert len(other._project(a, ("1.wq", "1.wk", "1.wv"))) == 3
+    top = base.abs().max()
+    assert (twice - other.last_logits(ids, {0})).abs().max() <= 2e-2 * top
+    swapped = _stack()
+    swapped.w["0.wg"], swapped.w["0.wu"] = swapped.w["0.wu"], swapped.w["0.wg"]
+    plain = _stack()
+    plain.w["0.wg"], plain.w["0.wu"] = plain.w["0.wu"], plain.w["0.wg"]
+    plain._fused = lambda *x: False
+    assert (swapped.last_logits(ids, {0}) - plain.last_logits(ids, {0})).abs().max() <= 2e-2 * top
