@@ -221,8 +221,9 @@ int bf1_plan_transposed(int64_t n, int32_t B, int32_t L,
  * with G * B >= 128 (so G = 1 needs B = 128); others return BF1_ERR_UNSUPPORTED.
  * Four kernels on `stream`: D and LSE log2 e per query row (to the
  * workspace); dK/dV over the transposed route (cut into segments of at most
- * 16 query blocks; the segments of long lists -- block 0 -- leave partial
- * sums in the workspace), which also writes dS (bf16, one 8 KB unit per
+ * 16 query blocks, fewer where the whole call has little work; the segments
+ * of a split list after its first leave partial sums in the workspace or, for
+ * the shorter cuts, in dQ, which is written last), which also writes dS (bf16, one 8 KB unit per
  * selected block pair, q-head and pair of 64-row sub-tiles) to the workspace;
  * a fixed-order sum of the partials; and dQ = dS K / sqrt(d) from the stored
  * dS along the forward route.  The workspace therefore grows with the number

@@ -165,81 +165,120 @@ int get_plan(int64_t n, int32_t B, int32_t L, hipStream_t s, Plan* out) {
 
 // ---- backward plan: transposed route cut into segments ---------------------
 // Every 64-key tile (key block i, sub-tile u, starting before n) gets the list
-// of query blocks that select block i; lists longer than SEG_MAX entries are
-// cut into segments whose partial dK/dV go to numbered workspace slots and are
-// summed by the reduce kernel.  Segments are ordered longest first.
+// of query blocks that select block i.  Lists longer than a segment length are
+// cut into segments: the first one writes dK/dV, the others leave partial sums
+// in numbered slots, which the reduce kernel adds in order.  Segments are
+// ordered longest first.
+//
+// A workgroup walks one segment, so its length sets the longest chain.  Long
+// sequences have work for every compute unit whatever the cut; there only
+// block 0's list (every query block) exceeds 16 entries, and its partial tiles
+// lie in the workspace (bf1_attn_bwd_workspace_size counts them).  Short ones
+// leave most units idle behind that chain, so they are cut to about the
+// entries a workgroup slot gets when all slots share the work, and the partial
+// tiles lie in dQ, which the dQ kernel overwrites last.  Whole backward on
+// MI355X, us, cut at 16 / for half / for exactly / for twice the 512 slots
+// there are (16/8 heads of 128 unless said): 1K tokens 75 / 42 / 42 / 42, 2K
+// 85 / 55 / 61 / 61, 4K 106 / 105 / 94 / 103, 4K at width 128 167 / 145 / 124 /
+// 138, 4 x 1K 95 / 86 / 72 / 88, 2 x 1500 tokens of 8/2 heads of 64 106 / 43 /
+// 43 / 43; from 8K on the share exceeds 16 entries and nothing changes.
 constexpr int64_t SEG_MAX = 16;
+constexpr int64_t SEG_LENGTHS[] = {1, 2, 3, 4, 6, 8, 12, SEG_MAX};
+constexpr int SEG_KINDS = sizeof(SEG_LENGTHS) / sizeof(SEG_LENGTHS[0]);
+constexpr int64_t BWD_SLOTS = 512;  // two resident dK/dV workgroups on each of 256 compute units
 
-struct BwdLayout {
-    std::vector<int32_t> users, uoffs, segs, reds;
-    int32_t nslots = 0;
-    int64_t nusers = 0;
-};
+// Entries per workgroup slot of a backward over bh (batch x kv-head) problems
+// (a list entry is B/64 query sub-tiles for each of B/64 key tiles).
+int64_t seg_wanted(int64_t nusers, int64_t nsub, int64_t bh) {
+    return (nusers * nsub * bh + BWD_SLOTS - 1) / BWD_SLOTS;
+}
 
-bool bwd_layout(int64_t n, int32_t B, int32_t L, BwdLayout* lay, bool fill) {
+// Transposed route sizes: entries, and partial slots of the cut at SEG_MAX with
+// a slot for every segment of a split list.
+bool bwd_sizes(int64_t n, int32_t B, int32_t L, int64_t* nusers, int64_t* nslots) {
     const int64_t NB = (n + B - 1) / B;
-    const int nsub = B / 64;
-    std::vector<int32_t> tmp;
-    std::vector<std::array<int32_t, 8>> segs;
-    int64_t nslots = 0, total = 0;
+    int64_t total = 0, slots = 0;
     for (int64_t i = 0; i < NB; ++i) {
         const int64_t cnt = bf1::route_users(NB, L, i, nullptr);
-        const int64_t off = total;
-        if (fill) lay->uoffs.push_back((int32_t)off);
-        if (fill) {
-            tmp.resize(cnt);
-            bf1::route_users(NB, L, i, tmp.data());
-            lay->users.insert(lay->users.end(), tmp.begin(), tmp.end());
-        }
         total += cnt;
         const int64_t nch = (cnt + SEG_MAX - 1) / SEG_MAX;
-        for (int u = 0; u < nsub; ++u) {
-            if (i * B + u * 64 >= n) break;
-            const int64_t slot0 = nch > 1 ? nslots : -1;
-            for (int64_t c = 0; c < nch; ++c) {
-                const int64_t m = std::min(SEG_MAX, cnt - SEG_MAX * c);
-                if (fill)
-                    segs.push_back({(int32_t)i, u, (int32_t)(off + SEG_MAX * c), (int32_t)m,
-                                    (int32_t)(nch > 1 ? slot0 + c : -1), 0, 0, 0});
-            }
-            if (nch > 1) {
-                if (fill) lay->reds.insert(lay->reds.end(), {(int32_t)i, u, (int32_t)slot0, (int32_t)nch});
-                nslots += nch;
-            }
-            if (nslots > 0x3fffffff || total > 0x3fffffff) return false;
-        }
+        if (nch > 1) slots += nch * std::min<int64_t>(B / 64, (n - i * B + 63) / 64);
+        if (slots > 0x3fffffff || total > 0x3fffffff) return false;
     }
-    if (fill) {
-        lay->uoffs.push_back((int32_t)total);
-        std::stable_sort(segs.begin(), segs.end(),
-                         [](const std::array<int32_t, 8>& a, const std::array<int32_t, 8>& b) {
-                             return a[3] > b[3];
-                         });
-        for (auto& sg : segs) lay->segs.insert(lay->segs.end(), sg.begin(), sg.end());
-    }
-    lay->nslots = (int32_t)nslots;
-    lay->nusers = total;
+    *nusers = total;
+    *nslots = slots;
     return true;
 }
 
-struct BwdPlan {
-    int32_t* users = nullptr;
-    int32_t* uoffs = nullptr;
-    int64_t nusers = 0;
+// Segments (int32 x 8: key block, sub-tile, first entry, count, slot, 0, 0, 0)
+// and reduce descriptors (int32 x 4: key block, sub-tile, first slot, count) of
+// the lists in uoffs cut at `len` entries; returns the number of slots.
+int64_t bwd_cut(int64_t n, int32_t B, const std::vector<int32_t>& uoffs, int64_t len, std::vector<int32_t>* segs,
+                std::vector<int32_t>* reds) {
+    std::vector<std::array<int32_t, 8>> sg;
+    int64_t nslots = 0;
+    for (int64_t i = 0; i + 1 < (int64_t)uoffs.size(); ++i) {
+        const int64_t off = uoffs[i], cnt = uoffs[i + 1] - off;
+        const int64_t nch = (cnt + len - 1) / len;
+        for (int u = 0; u < B / 64 && i * B + u * 64 < n; ++u) {
+            for (int64_t c = 0; c < nch; ++c)
+                sg.push_back({(int32_t)i, u, (int32_t)(off + len * c), (int32_t)std::min(len, cnt - len * c),
+                              (int32_t)(c > 0 ? nslots + c - 1 : -1), 0, 0, 0});
+            if (nch > 1) {
+                reds->insert(reds->end(), {(int32_t)i, u, (int32_t)nslots, (int32_t)(nch - 1)});
+                nslots += nch - 1;
+            }
+        }
+    }
+    std::stable_sort(sg.begin(), sg.end(), [](const std::array<int32_t, 8>& a, const std::array<int32_t, 8>& b) {
+        return a[3] > b[3];
+    });
+    for (auto& x : sg) segs->insert(segs->end(), x.begin(), x.end());
+    return nslots;
+}
+
+struct BwdCut {
+    int64_t len = 0;
     int32_t* segs = nullptr;
     int32_t* reds = nullptr;
     int32_t nseg = 0, nred = 0, nslots = 0;
 };
+struct BwdPlan {
+    int32_t* users = nullptr;
+    int32_t* uoffs = nullptr;
+    int64_t nusers = 0;
+    int ncuts = 0;               // ascending lengths, SEG_MAX last
+    BwdCut cuts[SEG_KINDS];
+
+    void release() {
+        (void)hipFree(users);
+        (void)hipFree(uoffs);
+        for (int c = 0; c < ncuts; ++c) {
+            (void)hipFree(cuts[c].segs);
+            (void)hipFree(cuts[c].reds);
+        }
+    }
+};
 std::map<std::tuple<int, int64_t, int32_t, int32_t>, BwdPlan> g_bwd_plans;
+
+// The cut of a call: the shortest segments that still give every slot its
+// share, if their partial tiles fit dQ (nslots x 2 x 64 rows against the G n
+// rows of a kv-head).
+const BwdCut& pick_cut(const BwdPlan& p, int64_t n, int32_t B, int64_t bh, int64_t G) {
+    const int64_t want = seg_wanted(p.nusers, B / 64, bh);
+    int c = 0;
+    while (c + 1 < p.ncuts && (p.cuts[c].len < want || (int64_t)p.cuts[c].nslots * 128 > G * n)) ++c;
+    return p.cuts[c];
+}
 
 int bwd_workspace_bytes(int32_t batch, int64_t n, int32_t Hq, int32_t Hkv, int32_t head_dim, int32_t B,
                         int32_t L, int64_t* bytes) {
-    BwdLayout lay;
-    if (!bwd_layout(n, B, L, &lay, false)) return BF1_ERR_INVALID_ARG;
+    int64_t nusers, nslots;
+    if (!bwd_sizes(n, B, L, &nusers, &nslots)) return BF1_ERR_INVALID_ARG;
     const int64_t delta = ((int64_t)batch * Hq * n * 4 + 255) / 256 * 256;
-    const int64_t part = (int64_t)batch * Hkv * lay.nslots * 2 * 64 * head_dim * 4;
+    const int64_t part = (int64_t)batch * Hkv * nslots * 2 * 64 * head_dim * 4;
     const int64_t nsub = B / 64;
-    const int64_t ds = (int64_t)batch * Hq * lay.nusers * nsub * nsub * 64 * 64 * 2;
+    const int64_t ds = (int64_t)batch * Hq * nusers * nsub * nsub * 64 * 64 * 2;
     *bytes = 2 * delta + part + ds;  // D, LSE * log2 e, partial tiles, dS units
     return BF1_OK;
 }
@@ -255,13 +294,17 @@ int get_bwd_plan(int64_t n, int32_t B, int32_t L, hipStream_t s, BwdPlan* out) {
         int st = capturing(s, &cap);
         if (st != BF1_OK) return st;
         if (cap) return BF1_ERR_CAPTURE;
-        BwdLayout lay;
-        if (!bwd_layout(n, B, L, &lay, true)) return BF1_ERR_INVALID_ARG;
+        int64_t nslots;
         BwdPlan p;
-        p.nseg = (int32_t)(lay.segs.size() / 8);
-        p.nred = (int32_t)(lay.reds.size() / 4);
-        p.nslots = lay.nslots;
-        p.nusers = lay.nusers;
+        if (!bwd_sizes(n, B, L, &p.nusers, &nslots)) return BF1_ERR_INVALID_ARG;
+        const int64_t NB = (n + B - 1) / B;
+        std::vector<int32_t> users(p.nusers), uoffs;
+        int64_t at = 0;
+        for (int64_t i = 0; i < NB; ++i) {
+            uoffs.push_back((int32_t)at);
+            at += bf1::route_users(NB, L, i, users.data() + at);
+        }
+        uoffs.push_back((int32_t)at);
         auto up = [](const std::vector<int32_t>& v, int32_t** d) -> bool {
             const size_t bytes = sizeof(int32_t) * (v.empty() ? 1 : v.size());
             if (hipMalloc((void**)d, bytes) != hipSuccess) return false;
@@ -270,12 +313,21 @@ int get_bwd_plan(int64_t n, int32_t B, int32_t L, hipStream_t s, BwdPlan* out) {
                 return false;
             return true;
         };
-        if (!up(lay.users, &p.users) || !up(lay.uoffs, &p.uoffs) || !up(lay.segs, &p.segs) ||
-            !up(lay.reds, &p.reds)) {
-            (void)hipFree(p.users);
-            (void)hipFree(p.uoffs);
-            (void)hipFree(p.segs);
-            (void)hipFree(p.reds);
+        bool ok = up(users, &p.users) && up(uoffs, &p.uoffs);
+        // every cut that some batch and head count can ask for is made now, so
+        // that later calls of any of them find it (also under capture)
+        for (int k = 0; k < SEG_KINDS && ok; ++k) {
+            if (SEG_LENGTHS[k] != SEG_MAX && SEG_LENGTHS[k] < seg_wanted(p.nusers, B / 64, 1)) continue;
+            std::vector<int32_t> segs, reds;
+            BwdCut& c = p.cuts[p.ncuts++];
+            c.len = SEG_LENGTHS[k];
+            c.nslots = (int32_t)bwd_cut(n, B, uoffs, c.len, &segs, &reds);
+            c.nseg = (int32_t)(segs.size() / 8);
+            c.nred = (int32_t)(reds.size() / 4);
+            ok = up(segs, &c.segs) && up(reds, &c.reds);
+        }
+        if (!ok) {
+            p.release();
             return BF1_ERR_NOMEM;
         }
         it = g_bwd_plans.emplace(key, p).first;
@@ -551,12 +603,13 @@ int bf1_attn_bwd(const void* Q, const void* K, const void* V, const void* O, con
     const int64_t delta_bytes = ((int64_t)batch * Hq * n * 4 + 255) / 256 * 256;
     float* delta = (float*)workspace;
     float* lse2 = (float*)((char*)workspace + delta_bytes);
-    float* part = (float*)((char*)workspace + 2 * delta_bytes);
-    void* ds = (char*)workspace + 2 * delta_bytes +
-               (int64_t)batch * Hkv * bp.nslots * 2 * 64 * head_dim * 4;
+    const int64_t ds_bytes = (int64_t)batch * Hq * bp.nusers * (B / 64) * (B / 64) * 64 * 64 * 2;
+    void* ds = (char*)workspace + need - ds_bytes;
+    const BwdCut& cut = pick_cut(bp, n, B, (int64_t)batch * Hkv, Hq / Hkv);
+    float* part = cut.len == SEG_MAX ? (float*)((char*)workspace + 2 * delta_bytes) : dQ;
     bf1::BwdArgs a{Q, K, V, O, dO, LSE, dQ, dK, dV, delta, lse2, part, ds,
-                   plan.row_ptr, plan.col_idx, plan.nnz, bp.users, bp.uoffs, bp.nusers, bp.segs, bp.nseg,
-                   bp.reds, bp.nred, bp.nslots, batch, n, Hq, Hkv, B, head_dim, L};
+                   plan.row_ptr, plan.col_idx, plan.nnz, bp.users, bp.uoffs, bp.nusers, cut.segs, cut.nseg,
+                   cut.reds, cut.nred, cut.nslots, batch, n, Hq, Hkv, B, head_dim, L};
     return status_of(bf1::launch_backward(a, s));
 }
 
@@ -574,12 +627,7 @@ void bf1_release_plans(void) {
         (void)hipFree(kv.second.col_idx);
     }
     g_plans.clear();
-    for (auto& kv : g_bwd_plans) {
-        (void)hipFree(kv.second.users);
-        (void)hipFree(kv.second.uoffs);
-        (void)hipFree(kv.second.segs);
-        (void)hipFree(kv.second.reds);
-    }
+    for (auto& kv : g_bwd_plans) kv.second.release();
     g_bwd_plans.clear();
 }
 

@@ -11,10 +11,11 @@
 //    segment of the tile's query-block list), walking the TRANSPOSED route
 //    (the query blocks that select the key block); two waves accumulate dV
 //    and two dK in registers, and the dS it forms is written to the workspace
-//    for dQ.  Key block 0 is selected by every query block, so long lists
-//    are cut into segments whose partial sums go to a workspace.
-//  * bwd_reduce_kernel -- sums the segment partials of such tiles in a fixed
-//    order (deterministic) into dK and dV.
+//    for dQ.  Long lists (key block 0 is selected by every query block), and
+//    in short calls most lists, are cut into segments; those after a list's
+//    first leave partial sums.
+//  * bwd_reduce_kernel -- adds the segment partials of such tiles in a fixed
+//    order (deterministic) to dK and dV.
 //  * bwd_dq_kernel   -- one workgroup per (batch, kv-head, query block, row
 //    chunk), walking the forward route like the forward kernel: dQ from the
 //    stored dS and the K tiles (no score is recomputed).
@@ -579,7 +580,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dkdv_kernel(
     }
 }
 
-// Sum of the partial slots of split key tiles: reduce descriptor (int32 x 4) =
+// Adds the partial slots of split key tiles to dK and dV: reduce descriptor (int32 x 4) =
 // key block, sub-tile, first slot, slot count.  Fixed summation order.  One
 // workgroup per (descriptor, batch x kv-head, 256-element chunk of the 64 x D
 // tile); each thread sums one element of dK and of dV over the slots.
@@ -601,8 +602,10 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(
     const int key = e / BD, d = e % BD;
     const int32_t kp = i * BW + u * KT + key;
     const float* pk = part + ((int64_t)bh * nslots + s0) * SLOT + e;
-    // slots summed in order; eight slots' loads are issued before their sums
-    float sk = 0.f, sv = 0.f;
+    // the first segment's sums are in dK and dV already; slots are added in
+    // order, eight slots' loads issued before their sums
+    const int64_t at = (kvrow0 + kp) * BD + d;
+    float sk = kp < n ? dK[at] : 0.f, sv = kp < n ? dV[at] : 0.f;
     int32_t s = 0;
     for (; s + 8 <= ns; s += 8) {
         float kk[8], vv[8];
@@ -622,8 +625,8 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(
         sv += pk[s * SLOT + KT * BD];
     }
     if (kp < n) {
-        dK[(kvrow0 + kp) * BD + d] = sk;
-        dV[(kvrow0 + kp) * BD + d] = sv;
+        dK[at] = sk;
+        dV[at] = sv;
     }
 }
 

@@ -39,7 +39,7 @@ struct BwdArgs {
     float* dV;
     float* delta;            // workspace: [batch, Hq, n] fp32 (D = rowsum(dO * O))
     float* lse2;             // workspace: [batch, Hq, n] fp32 (LSE * log2 e)
-    float* part;             // workspace: [batch * Hkv, nslots, 2, 64, head_dim] fp32
+    float* part;             // workspace or dQ: [batch * Hkv, nslots, 2, 64, head_dim] fp32
     void* ds;                // workspace: dS units, [batch * Hkv, nusers, B/64, B/64, Hq/Hkv] x 8 KB bf16
     const int32_t* row_ptr;  // forward route (CSR)
     const int32_t* col_idx;
