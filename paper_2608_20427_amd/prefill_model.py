@@ -167,7 +167,7 @@ class PrefillStack:
         """h <- h + r in place (if r is given), then RMSNorm(h) * gain."""
         out = torch.empty_like(h)
         _check(load().bf1_stack_rms(_ptr(h), _ptr(r), _ptr(gain), _ptr(out), h.shape[0], h.shape[1], self.cfg.eps,
-                                    _stream(None)), "bf1_stack_rms")
+                                    _stream(None, h.device)), "bf1_stack_rms")
         return out
 
     def _layer_fused(self, l, h, r, cos, sin, bf1_layers, dense_attention):
@@ -181,19 +181,19 @@ class PrefillStack:
         Q, K, V = (torch.empty((1, x, n, d), dtype=h.dtype, device=h.device) for x in (H, Hkv, Hkv))
         _check(lib.bf1_stack_heads(_ptr(q), _ptr(k), _ptr(v), q.stride(0), k.stride(0), v.stride(0),
                                    _ptr(w[p + "q_norm"]), _ptr(w[p + "k_norm"]), _ptr(cos), _ptr(sin), _ptr(Q),
-                                   _ptr(K), _ptr(V), n, H, Hkv, d, cfg.eps, _stream(None)), "bf1_stack_heads")
+                                   _ptr(K), _ptr(V), n, H, Hkv, d, cfg.eps, _stream(None, h.device)), "bf1_stack_heads")
         if l not in bf1_layers and dense_attention is not None:
             O = dense_attention(Q, K, V)[0].transpose(0, 1).reshape(n, H * d)
         else:
             O = torch.empty((n, H * d), dtype=h.dtype, device=h.device)
             _check(lib.bf1_attn_fwd_token_major(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), 1, n, H, Hkv, d, int(self.B),
-                                                int(self.L), int(l not in bf1_layers), _stream(None)),
+                                                int(self.L), int(l not in bf1_layers), _stream(None, h.device)),
                    "bf1_attn_fwd_token_major")
         a = self._rms_fused(h, O @ w[p + "wo"], w[p + "post_norm"])
         g, u = self._project(a, (p + "wg", p + "wu"))
         s = torch.empty(g.shape, dtype=g.dtype, device=g.device)
         _check(lib.bf1_stack_swiglu(_ptr(g), _ptr(u), g.stride(0), u.stride(0), _ptr(s), n, g.shape[1],
-                                    _stream(None)), "bf1_stack_swiglu")
+                                    _stream(None, h.device)), "bf1_stack_swiglu")
         return s @ w[p + "wd"]
 
     def last_logits(self, ids, bf1_layers, dense_attention=None):
