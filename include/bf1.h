@@ -94,9 +94,9 @@ int bf1_plan(int64_t n, int32_t B, int32_t L,
 
 /*
  * BF1 prefill forward (§3.1): O and LSE for every (batch, q-head, token).
- * The route is built by the planner on first use for (device, n, B, L) and
- * kept in a library-owned cache (see bf1_release_plans); the attention
- * kernel then walks only the selected key blocks of each query block.
+ * The route's plan is built on first use for (device, n, B, L) and kept in a
+ * library-owned cache (see bf1_release_plans), where the backward finds it;
+ * the attention kernel walks only the selected key blocks of each query block.
  * LSE may be NULL (not written).
  */
 int bf1_attn_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
@@ -107,19 +107,11 @@ int bf1_attn_fwd(const void* Q, const void* K, const void* V, void* O, float* LS
  * For callers that cannot allocate device memory -- code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc: the BF1
  * prefill forward of bf1_attn_fwd, same arguments, same kernels and bitwise
- * the same results, with no allocation and no plan cache.  Each call runs the
- * route planner into a fixed scratch array owned by the library (one
- * 4 MiB __device__ array of int32, 2^20 entries, per device, held until the
- * process ends) and then the attention kernel over that table, both on
- * `stream`.  The table must fit: NB + 1 + nnz <= 2^20 (bf1_plan_size gives
+ * the same results, with no allocation and no plan cache: one kernel, which
+ * walks the route of Eq. 1 in closed form and shares nothing with other calls.
+ * The route's table must have NB + 1 + nnz <= 2^20 entries (bf1_plan_size gives
  * NB and nnz; at B = 64, L = 2 this allows n up to about 2M tokens), else
- * BF1_ERR_BUFFER_TOO_SMALL is returned before anything is enqueued.  No
- * scratch content needs clearing: the planner rewrites every entry the
- * kernel reads.  All calls on one device share its array, so calls that
- * overlap in time on one device (on different streams, or from several
- * threads without ordering) race and may read each other's tables; calls
- * ordered on one stream do not.  The first call on a device looks the
- * array's address up (no allocation).
+ * BF1_ERR_BUFFER_TOO_SMALL is returned before anything is enqueued.
  */
 int bf1_attn_fwd_noalloc(const void* Q, const void* K, const void* V, void* O, float* LSE,
                          int32_t batch, int64_t n, int32_t Hq, int32_t Hkv, int32_t head_dim,

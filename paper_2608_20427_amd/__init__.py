@@ -269,9 +269,8 @@ def attn_fwd(q, k, v, B=64, L=2, out=None, lse=None, want_lse=True, stream=None)
 
 
 def attn_fwd_noalloc(q, k, v, out, lse=None, B=64, L=2, stream=None):
-    """BF1 prefill forward that allocates no device memory (the route table
-    goes to the library's fixed scratch array): the caller passes O (and
-    optionally LSE); returns (O, LSE)."""
+    """BF1 prefill forward that allocates no device memory: the caller passes O
+    (and optionally LSE); returns (O, LSE)."""
     if out is None:
         raise ValueError("attn_fwd_noalloc writes into a caller-provided out")
     out, lse, (batch, n, Hq, Hkv, d) = _prep(q, k, v, out, lse, False)

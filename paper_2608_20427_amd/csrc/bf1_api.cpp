@@ -389,11 +389,12 @@ int bf1_attn_fwd(const void* Q, const void* K, const void* V, void* O, float* LS
     if (B != 64 && B != 128) return BF1_ERR_UNSUPPORTED;
     if (batch == 0 || n == 0) return BF1_OK;
     hipStream_t s = (hipStream_t)stream;
+    // The kernel walks Eq. 1 itself; the plan call keeps what the interface says
+    // about a route's first use (no such call under capture, sizes, errors).
     Plan plan;
     st = get_plan(n, B, L, s, &plan);
     if (st != BF1_OK) return st;
-    bf1::AttnArgs a{Q, K, V, O, LSE, plan.row_ptr, plan.col_idx, plan.nnz,
-                    batch, n, Hq, Hkv, head_dim, B, false};
+    bf1::AttnArgs a{Q, K, V, O, LSE, nullptr, nullptr, plan.nnz, batch, n, Hq, Hkv, head_dim, B, L, false};
     return run_attn(a, s);
 }
 
@@ -408,16 +409,8 @@ int bf1_attn_fwd_noalloc(const void* Q, const void* K, const void* V, void* O, f
     int64_t NB, nnz;
     if (!route_sizes(n, B, L, &NB, &nnz)) return BF1_ERR_INVALID_ARG;
     if (NB + 1 + nnz > bf1::kNoallocInts) return BF1_ERR_BUFFER_TOO_SMALL;
-    int32_t* table = nullptr;
-    if (bf1::noalloc_scratch(&table) != hipSuccess) return BF1_ERR_HIP;
-    int32_t* row_ptr = table;
-    int32_t* col_idx = table + (NB + 1);
-    hipStream_t s = (hipStream_t)stream;
-    // The planner rewrites every entry the attention kernel reads, so nothing
-    // left in the scratch by an earlier call matters.
-    if (bf1::launch_plan((int32_t)NB, L, row_ptr, col_idx, s) != hipSuccess) return BF1_ERR_HIP;
-    bf1::AttnArgs a{Q, K, V, O, LSE, row_ptr, col_idx, nnz, batch, n, Hq, Hkv, head_dim, B, false};
-    return run_attn(a, s);
+    bf1::AttnArgs a{Q, K, V, O, LSE, nullptr, nullptr, nnz, batch, n, Hq, Hkv, head_dim, B, L, false};
+    return run_attn(a, (hipStream_t)stream);
 }
 
 int bf1_attn_fwd_csr(const void* Q, const void* K, const void* V, void* O, float* LSE,
@@ -431,7 +424,7 @@ int bf1_attn_fwd_csr(const void* Q, const void* K, const void* V, void* O, float
     if (batch == 0 || n == 0) return BF1_OK;
     if (!row_ptr || (nnz > 0 && !col_idx)) return BF1_ERR_INVALID_ARG;
     if (!aligned(row_ptr, 4) || (col_idx && !aligned(col_idx, 4))) return BF1_ERR_INVALID_ARG;
-    bf1::AttnArgs a{Q, K, V, O, LSE, row_ptr, col_idx, nnz, batch, n, Hq, Hkv, head_dim, B, false};
+    bf1::AttnArgs a{Q, K, V, O, LSE, row_ptr, col_idx, nnz, batch, n, Hq, Hkv, head_dim, B, 0, false};
     return run_attn(a, (hipStream_t)stream);
 }
 
@@ -441,7 +434,7 @@ int bf1_dense_causal_fwd(const void* Q, const void* K, const void* V, void* O, f
     int st = check_attn(Q, K, V, O, LSE, batch, n, Hq, Hkv, head_dim);
     if (st != BF1_OK) return st;
     if (batch == 0 || n == 0) return BF1_OK;
-    bf1::AttnArgs a{Q, K, V, O, LSE, nullptr, nullptr, 0, batch, n, Hq, Hkv, head_dim, 64, true};
+    bf1::AttnArgs a{Q, K, V, O, LSE, nullptr, nullptr, 0, batch, n, Hq, Hkv, head_dim, 64, 0, true};
     return run_attn(a, (hipStream_t)stream);
 }
 
@@ -460,8 +453,8 @@ int bf1_attn_fwd_token_major(const void* Q, const void* K, const void* V, void* 
         st = get_plan(n, B, L, s, &plan);
         if (st != BF1_OK) return st;
     }
-    bf1::AttnArgs a{Q, K, V, O, nullptr, plan.row_ptr, plan.col_idx, plan.nnz,
-                    batch, n, Hq, Hkv, head_dim, dense ? 64 : B, dense == 1};
+    bf1::AttnArgs a{Q, K, V, O, nullptr, nullptr, nullptr, plan.nnz, batch, n, Hq, Hkv, head_dim,
+                    dense ? 64 : B, L, dense == 1};
     a.token_major = true;
     return run_attn(a, s);
 }

@@ -12,15 +12,16 @@ struct AttnArgs {
     const void* V;
     void* O;
     float* LSE;             // may be null
-    const int32_t* row_ptr; // null for the dense route
+    const int32_t* row_ptr; // a caller's table; null: the route of Eq. 1 (or the dense one)
     const int32_t* col_idx;
-    int64_t nnz;
+    int64_t nnz;            // entries of the route's table
     int32_t batch;
     int64_t n;
     int32_t Hq;
     int32_t Hkv;
     int32_t head_dim;       // 64 or 128
     int32_t B;              // block width 64 or 128 (BF1 route)
+    int32_t L;              // local width of the route of Eq. 1
     bool dense;             // implicit route {0..j} over 64-token blocks
     int32_t key_split = 0;  // 0 automatic, 1 one key group, 2 two key groups per workgroup
     bool token_major = false;  // O is [batch, n, Hq, head_dim] instead of [batch, Hq, n, head_dim]
@@ -101,11 +102,8 @@ struct DecodeArgs {
 };
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream);
 
-// Fixed device scratch of the forward that allocates nothing: capacity in
-// int32 entries (row_ptr and col_idx of one route table), and the address of
-// the current device's copy (looked up once per device, then cached).
-constexpr int64_t kNoallocInts = int64_t(1) << 20;  // 4 MiB
-hipError_t noalloc_scratch(int32_t** ptr);
+// Largest route table (row_ptr and col_idx entries) bf1_attn_fwd_noalloc accepts.
+constexpr int64_t kNoallocInts = int64_t(1) << 20;
 
 // Route planner: row_ptr[0..NB], col_idx[0..nnz) on `stream`.
 hipError_t launch_plan(int32_t NB, int32_t L, int32_t* row_ptr, int32_t* col_idx,

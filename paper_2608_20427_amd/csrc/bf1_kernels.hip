@@ -3,9 +3,9 @@
 // Two kernels:
 //  * bf1_plan_kernel -- the integer route planner (paper §3.1, Eq. 1): one
 //    thread per query block writes its CSR row in closed form.
-//  * attn_fwd_kernel -- flash-style prefill forward over a block route.  The
-//    BF1 instance walks the CSR row of its query block; the dense instance
-//    walks every block 0..j (the dense causal comparator).
+//  * attn_fwd_kernel -- flash-style prefill forward over a block route: Eq. 1
+//    in closed form, a caller's CSR table, or every block 0..j (the dense
+//    causal comparator).
 //
 // Work decomposition.  One workgroup handles one (batch, kv-head, query
 // block, row chunk): the G q-heads of a GQA group are stacked, so G*B query
@@ -54,31 +54,11 @@ __global__ void bf1_plan_kernel(int32_t NB, int32_t L, int32_t* __restrict__ row
     const int64_t start = route_row_start(j, L);
     row_ptr[j] = (int32_t)start;
     if (j == NB) return;
-    // Ascending emission: global block 0, dyadic predecessors j - 2^r for
-    // descending r (offsets above L only; smaller ones are local), the local
-    // window j-min(j,L) .. j-1, then the self block.  Values that repeat the
-    // last one written (block 0 reached again) are dropped.
     // Writes stop at the closed-form end of the row, so the table can never
     // be overrun.
     const int64_t end = route_row_start(j + 1, L);
     int64_t e = start;
-    int32_t last = 0;
-    if (e < end) col_idx[e++] = 0;
-    if (j == 0) return;
-    int rmax = 31 - __builtin_clz((unsigned)j);
-    for (int r = rmax; r >= 2; --r) {
-        const int32_t off = 1 << r;
-        if (off > L) {
-            const int32_t v = j - off;
-            if (v > last && e < end) { col_idx[e++] = v; last = v; }
-        }
-    }
-    const int32_t nloc = j < L ? j : L;
-    for (int32_t l = nloc; l >= 1; --l) {
-        const int32_t v = j - l;
-        if (v > last && e < end) { col_idx[e++] = v; last = v; }
-    }
-    if (e < end) col_idx[e] = j;
+    for (int32_t o = j; o >= 0 && e < end; o = route_next_offset(o, L)) col_idx[e++] = j - o;
 }
 
 // ---------------------------------------------------------------------------
@@ -158,6 +138,7 @@ __device__ __forceinline__ void lds_read_tr16_x8(uint32_t addr, u32x2 (&v)[8]) {
 // argument segment only in the epilogue, through a pointer the compiler cannot
 // see through: held from the start it costs scalar registers for the whole
 // loop, which is out of them (100 in use, the rest spilled to vector lanes).
+enum class Route { CSR, BF1, DENSE };  // a caller's table, Eq. 1 in closed form, every block 0..j
 struct OutArgs {
     __bf16* O;
     float* LSE;      // may be null
@@ -172,11 +153,11 @@ __device__ __forceinline__ OutArgs out_args() {
     return OutArgs{a->O, a->LSE, a->o_tok, a->o_head};
 }
 
-template <int D, int G, int BW, int NW, bool DENSE, int KSPLIT>
+template <int D, int G, int BW, int NW, Route ROUTE, int KSPLIT>
 __global__ __launch_bounds__(NW * 64 * KSPLIT, KSPLIT == 1 ? 2 : 1) void attn_fwd_kernel(
     OutArgs, const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int64_t nnz, int32_t n,
-    int32_t NB, int32_t batch_hkv, int32_t Hkv, float c_log2) {
+    int32_t NB, int32_t L, int32_t batch_hkv, int32_t Hkv, float c_log2) {
     constexpr int ROWS = NW * 32;             // stacked query rows per workgroup
     constexpr int NCHUNK = (G * BW + ROWS - 1) / ROWS;
     constexpr int NSUB = BW / KT;             // LDS tiles per key block
@@ -236,39 +217,54 @@ __global__ __launch_bounds__(NW * 64 * KSPLIT, KSPLIT == 1 ? 2 : 1) void attn_fw
     }
 
     // ---- route walk ---------------------------------------------------------
-    int32_t pos_end, cur_p;
-    if (DENSE) {
-        cur_p = 0;
-        pos_end = j + 1;
-    } else {
+    // Next tile of the route: a block i in [0, j] and a 64-key sub-tile of it
+    // that starts before n.  All quantities fit in 32 bits.
+    int32_t pos_end = 0;                                // CSR: end of the row
+    int32_t cur_p = ROUTE == Route::CSR ? 0 : j;        // CSR: entry; BF1: offset j - i; DENSE: j - i
+    int cur_u = 0;
+    if constexpr (ROUTE == Route::CSR) {
         int64_t e0 = row_ptr[j], e1 = row_ptr[j + 1];
         e0 = e0 < 0 ? 0 : (e0 > nnz ? nnz : e0);
         e1 = e1 < e0 ? e0 : (e1 > nnz ? nnz : e1);
         cur_p = (int32_t)e0;
         pos_end = (int32_t)e1;
     }
-    int cur_u = 0;
-    // Next tile of the route: a block i in [0, j] (caller tables may hold
-    // anything else; such entries are skipped) and a 64-key sub-tile of it
-    // that starts before n.  All quantities fit in 32 bits.  The table entry
-    // at cur_p is fetched one call ahead (pref), so the scalar load latency
-    // is hidden behind a pipeline step.
-    int32_t pref = (!DENSE && cur_p < pos_end) ? col_idx[cur_p] : -1;
+    // Caller tables may hold anything; entries outside [0, j] are skipped.  The
+    // entry at cur_p is fetched one call ahead (pref), so the scalar load
+    // latency is hidden behind a pipeline step.
+    int32_t pref = (ROUTE == Route::CSR && cur_p < pos_end) ? col_idx[cur_p] : -1;
     auto advance = [&]() {
         ++cur_p;
         cur_u = 0;
         pref = (cur_p < pos_end) ? col_idx[cur_p] : -1;
     };
+    // sub-tiles of the self block that start before n
+    const int self_tiles = NSUB == 1 ? 1 : min(NSUB, (n - j * BW + KT - 1) / KT);
     auto next_tile = [&](int32_t& ti, int& tu) -> bool {
-        if constexpr (DENSE) {
+        if constexpr (ROUTE == Route::DENSE) {
             // Every block 0..j exists and is one tile.  Without this the
             // compiler unrolls the search below into some 60 scalar
             // instructions per tile beside the matrix products (8K tokens,
             // Qwen geometry: 277 us with the search, 262 us without).
-            static_assert(!DENSE || NSUB == 1, "the dense route is walked in blocks of one tile");
-            ti = cur_p;
+            static_assert(ROUTE != Route::DENSE || NSUB == 1, "the dense route is walked in blocks of one tile");
+            ti = j - cur_p;
             tu = 0;
-            return cur_p++ < pos_end;
+            return cur_p-- >= 0;
+        }
+        if constexpr (ROUTE == Route::BF1) {
+            // Eq. 1 in closed form: no table, so a workgroup's first K/V load
+            // does not wait for two dependent loads (one layer, 16/8 heads of
+            // 128: 1K tokens 11.7 -> 11.1 us, 2 x 30001 401 -> 393 us, 64K at
+            // width 128 765 -> 755 us), and the no-allocation entry needs no
+            // planner launch (1K tokens 14.4 -> 11.1 us).
+            if (cur_p < 0) return false;
+            ti = j - cur_p;
+            tu = cur_u;
+            if (NSUB == 1 || ++cur_u >= (cur_p == 0 ? self_tiles : NSUB)) {
+                cur_u = 0;
+                cur_p = route_next_offset(cur_p, L);
+            }
+            return true;
         }
         while (cur_p < pos_end) {
             const int32_t i = pref;
@@ -713,7 +709,7 @@ bool use_key_split(int mode, int64_t items, int64_t tiles) {
     return cu > 0 && items <= cu;
 }
 
-template <int D, int G, int BW, bool DENSE>
+template <int D, int G, int BW, Route ROUTE>
 hipError_t launch_attn(const AttnArgs& a, hipStream_t stream) {
     constexpr int NW = (G * BW) >= 128 ? 4 : (G * BW) / 32;
     constexpr int ROWS = NW * 32;
@@ -726,17 +722,17 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t stream) {
     const OutArgs out{(__bf16*)a.O, a.LSE, a.token_major ? a.Hq : 1, a.token_major ? 1 : (int32_t)a.n};
     // key tiles the launch walks (the dense route {0..j} has NB (NB + 1) / 2
     // blocks per kv-head; a caller table is taken at its size)
-    const int64_t blocks = DENSE ? (int64_t)NB * (NB + 1) / 2 : a.nnz;
+    const int64_t blocks = ROUTE == Route::DENSE ? (int64_t)NB * (NB + 1) / 2 : a.nnz;
     const int64_t tiles = blocks * (BW / KT) * a.batch * a.Hkv * NCHUNK;
     if (use_key_split(a.key_split, items, tiles)) {
-        hipLaunchKernelGGL((attn_fwd_kernel<D, G, BW, NW, DENSE, 2>), dim3((unsigned)items),
+        hipLaunchKernelGGL((attn_fwd_kernel<D, G, BW, NW, ROUTE, 2>), dim3((unsigned)items),
                            dim3(2 * NW * 64), 0, stream, out, (const __bf16*)a.Q, (const __bf16*)a.K,
-                           (const __bf16*)a.V, a.row_ptr, a.col_idx, a.nnz, (int32_t)a.n, NB,
+                           (const __bf16*)a.V, a.row_ptr, a.col_idx, a.nnz, (int32_t)a.n, NB, a.L,
                            a.batch * a.Hkv, a.Hkv, c_log2);
     } else {
-        hipLaunchKernelGGL((attn_fwd_kernel<D, G, BW, NW, DENSE, 1>), dim3((unsigned)items),
+        hipLaunchKernelGGL((attn_fwd_kernel<D, G, BW, NW, ROUTE, 1>), dim3((unsigned)items),
                            dim3(NW * 64), 0, stream, out, (const __bf16*)a.Q, (const __bf16*)a.K,
-                           (const __bf16*)a.V, a.row_ptr, a.col_idx, a.nnz, (int32_t)a.n, NB,
+                           (const __bf16*)a.V, a.row_ptr, a.col_idx, a.nnz, (int32_t)a.n, NB, a.L,
                            a.batch * a.Hkv, a.Hkv, c_log2);
     }
     return hipGetLastError();
@@ -744,9 +740,10 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t stream) {
 
 template <int D, int G>
 hipError_t dispatch_bw(const AttnArgs& a, hipStream_t s) {
-    if (a.dense) return launch_attn<D, G, 64, true>(a, s);
-    if (a.B == 64) return launch_attn<D, G, 64, false>(a, s);
-    return launch_attn<D, G, 128, false>(a, s);
+    if (a.dense) return launch_attn<D, G, 64, Route::DENSE>(a, s);
+    if (a.row_ptr == nullptr)
+        return a.B == 64 ? launch_attn<D, G, 64, Route::BF1>(a, s) : launch_attn<D, G, 128, Route::BF1>(a, s);
+    return a.B == 64 ? launch_attn<D, G, 64, Route::CSR>(a, s) : launch_attn<D, G, 128, Route::CSR>(a, s);
 }
 
 template <int D>
@@ -759,37 +756,7 @@ hipError_t dispatch_g(const AttnArgs& a, hipStream_t s) {
     }
 }
 
-// ---------------------------------------------------------------------------
-// Fixed scratch of the forward that allocates nothing
-// ---------------------------------------------------------------------------
-// The route table of bf1_attn_fwd_noalloc (row_ptr, then col_idx right after
-// it) lives in this array; each device holds its own copy for the life of the
-// process.  In host code the name is a stand-in for the symbol, never a
-// device address: the address of a device's copy comes from
-// hipGetSymbolAddress, taken once per device with that device current, and
-// only that address is handed to kernels.
-static __device__ __align__(256) int32_t scratch[kNoallocInts];
-
 }  // namespace
-
-hipError_t noalloc_scratch(int32_t** ptr) {
-    static std::mutex mu;
-    static std::map<int, int32_t*> addr;  // device -> address of its copy
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    std::lock_guard<std::mutex> lock(mu);
-    auto it = addr.find(dev);
-    if (it == addr.end()) {
-        void* p = nullptr;
-        e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (e != hipSuccess) return e;
-        if (p == nullptr) return hipErrorInvalidSymbol;
-        it = addr.emplace(dev, static_cast<int32_t*>(p)).first;
-    }
-    *ptr = it->second;
-    return hipSuccess;
-}
 
 hipError_t launch_plan(int32_t NB, int32_t L, int32_t* row_ptr, int32_t* col_idx,
                        hipStream_t stream) {

@@ -20,12 +20,23 @@
 
 namespace bf1 {
 
+// floor(log2 x), x >= 1
+BF1_HD int log2_floor(int64_t x) { return 63 - __builtin_clzll((unsigned long long)x); }
+
 // Number of r >= 2 with L < 2^r < lim  (strict) -- helper for prefix sums.
 BF1_HD int64_t dyadic_count_below(int64_t lim, int64_t L) {
-    int64_t c = 0;
-    for (int r = 2; r < 62 && (int64_t(1) << r) < lim; ++r)
-        if ((int64_t(1) << r) > L) ++c;
-    return c;
+    if (lim < 2) return 0;
+    const int lo = L < 4 ? 2 : log2_floor(L) + 1, hi = log2_floor(lim - 1);
+    return hi >= lo ? hi - lo + 1 : 0;
+}
+
+// The blocks of P(j) in ascending order are j - o for the offsets o = j, then
+// route_next_offset(o, L) until it is negative: block 0, the dyadic
+// predecessors from the farthest, the locals, the self block.
+BF1_HD int32_t route_next_offset(int32_t o, int32_t L) {
+    if (o <= L) return o - 1;
+    const int32_t p = 1 << (31 - __builtin_clz((unsigned)(o - 1) | 1u));  // largest 2^r < o (1 for o = 1)
+    return p > L && p > 3 ? p : L;
 }
 
 // Earlier selected blocks of query block j.
@@ -53,12 +64,13 @@ BF1_HD int64_t route_pred_count(int64_t j, int64_t L) {
 BF1_HD int64_t route_row_start(int64_t j, int64_t L) {
     int64_t s = j;
     s += (j <= L) ? j * (j - 1) / 2 : L * (L - 1) / 2 + L * (j - L);
-    for (int r = 2; r < 62 && (int64_t(1) << r) < j; ++r) {
-        int64_t off = int64_t(1) << r;
-        if (off > L) s += j - off;
+    const int64_t c = dyadic_count_below(j, L);
+    if (c > 0) {  // sum of c consecutive powers of two up to the last one below j
+        const int hi = log2_floor(j - 1);
+        s += c * j - ((int64_t(2) << hi) - (int64_t(1) << (hi - c + 1)));
     }
     int64_t g = j - L - 1;
-    s += (g > 0 ? g : 0) - dyadic_count_below(j, L);
+    s += (g > 0 ? g : 0) - c;
     return s;
 }
 
