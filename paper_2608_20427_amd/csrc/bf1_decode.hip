@@ -24,10 +24,9 @@
 //
 // Split kernel: one workgroup of four waves per (sequence, kv-head, split);
 // a split is `ppw` consecutive pages of the sequence's list (earlier pages,
-// then the self page).  Each wave takes a quarter of every page's keys: lanes
-// read 16-byte chunks of key rows (D / 8 lanes per row), form the G scores of
-// a row by a cross-lane sum, and keep an online softmax (log2 units) with the
-// matching V chunks.  The four waves merge in LDS; a split that covers the
+// then the self page).  Each wave takes 16 keys of every 64 as one matrix tile
+// and keeps an online softmax (log2 units).  The four waves merge in LDS; a
+// split that covers the
 // whole list writes O and LSE at once, otherwise it writes a partial record
 // (per q-head: max, sum, unnormalised O row).  Merge kernel: one workgroup
 // per (sequence, kv-head) with more than one split sums the records in split
@@ -39,6 +38,8 @@
 // the page holds there.
 #include <hip/hip_runtime.h>
 #include <math.h>
+
+#include <type_traits>
 
 #include "bf1_device.h"
 #include "bf1_kernels.h"
@@ -110,14 +111,6 @@ __global__ __launch_bounds__(PLAN_THREADS) void decode_plan_kernel(
     }
 }
 
-__device__ __forceinline__ void bf16x8_to_float(u32x4 w, float* f) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        f[2 * k] = __uint_as_float(w[k] << 16);
-        f[2 * k + 1] = __uint_as_float(w[k] & 0xffff0000u);
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Decode attention.
 // ---------------------------------------------------------------------------
@@ -149,164 +142,105 @@ __device__ __forceinline__ void write_nan(__bf16* O, float* LSE, int b, int Hq, 
     if (LSE != nullptr && tid < G) LSE[(int64_t)b * Hq + h * G + tid] = __builtin_nanf("");
 }
 
-// A unit of decode work for one wave: a quarter of a page (KPW consecutive
-// keys), read as NI wave-wide loads of K rows and of V rows; lane `lane` holds
-// the 16-byte chunk cch of key row rg of every load.
-template <int D, int PW>
+// A unit of decode work for one wave: 16 keys of a page, one 16x16x32 matrix
+// tile of scores per 32 dims.  A page has PW / 16 units; wave w takes units w,
+// w + 4.  Columns of the score tile are the q-heads of the group, repeated:
+// column c is head c % G, and c / G selects a part of that head's weight.
+//
+// Scores S = K Q^T: A = K rows straight from memory (lane l: key l % 16, 16-byte
+// chunk 4 s + l / 16 for k-step s), B = Q rows.  Lane l then holds the scores of
+// keys 4 (l / 16) + 0..3 and column l % 16, which is the B operand of
+// O^T += V^T P^T as it stands.  That product needs 16-bit weights, so a weight
+// goes in as three bf16 parts that add up to the fp32 value (each part the
+// rounded rest of the ones before: 24 bits), one part per column group; the
+// epilogue adds the groups' columns.  G = 8 has two column groups; the third
+// part takes a second product.  V^T comes from LDS by transpose reads: a V unit
+// is staged by direct buffer -> LDS loads, 32-byte slot s of key row r at
+// s ^ vslot(r) (conflict-free: the 16 rows of a read hit distinct banks).
+// Rows past the valid keys are zeros by the buffer range check, whatever the
+// page holds.
+//
+// Bound by memory: about 40 vector instructions per unit where one fma per head
+// and element took 400, which bounded groups of 8 and cost the others their
+// overlap.  128 registers (K rows single-buffered, refilled once the scores have
+// read them) keep four workgroups per compute unit; three with K double-buffered
+// (154 registers) were no faster for G = 8 and 2-12% slower for G <= 2.  Device
+// time per step with the same splits, us, before / now: 32 sequences, context
+// 64K, 16/8 heads of 128 25.1 / 23.2; 16/2 heads 30.8 / 18.3; 16 sequences of
+// 16/8 heads of 64 12.6 / 10.6; four dense lists of 32K 101 / 91.
+template <int D>
 struct Unit {
-    static constexpr int LPR = D / 8;    // lanes per key row (16 bytes each)
-    static constexpr int RPI = 64 / LPR;  // key rows per wave-wide load
-    static constexpr int KPW = PW / 4;    // keys per unit (a quarter page)
-    static constexpr int NI = KPW / RPI;  // loads per unit (for K, and for V)
-    static_assert(NI >= 1 && KPW % RPI == 0, "page width and head_dim mismatch");
+    static constexpr int KEYS = 16;
+    static constexpr int RB = 2 * D;            // bytes per key row
+    static constexpr int KS = D / 32;           // k-steps of the scores = K loads per unit
+    static constexpr int DT = D / 16;           // 16-wide d tiles of O
+    static constexpr int SEGS = KEYS * RB / 1024;  // direct V loads per unit
+    static constexpr int WAIT_NEXT = 0x0F70 | SEGS;  // vmcnt: all but the next unit's V loads
 };
-
-// K and V page rows are read once per decode step (a page is not shared
-// between the workgroups of a step), so the loads are non-temporal: they do
-// not displace other lines in L2.
-template <int D, int PW>
-__device__ __forceinline__ void load_unit(const __bf16* __restrict__ Kp, const __bf16* __restrict__ Vp,
-                                          int64_t page_base, int quarter, int rg, int cch, u32x4* kr,
-                                          u32x4* vr) {
-    using U = Unit<D, PW>;
-#pragma unroll
-    for (int i = 0; i < U::NI; ++i) {
-        const int key = quarter * U::KPW + i * U::RPI + rg;
-        kr[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(Kp + page_base + (int64_t)key * D + cch * 8));
-    }
-#pragma unroll
-    for (int i = 0; i < U::NI; ++i) {
-        const int key = quarter * U::KPW + i * U::RPI + rg;
-        vr[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(Vp + page_base + (int64_t)key * D + cch * 8));
-    }
+template <int D>
+__device__ __forceinline__ int vslot(int row) {
+    return D == 128 ? (row & 7) : ((row >> 1) & 3);
 }
 
-// Online softmax over one unit: the G scores of each key row (cross-lane sum
-// over the LPR lanes of the row), masked past nvalid keys of the page (their
-// V chunks zeroed), folded into the wave's running max / sum / row.
-template <int D, int G, int PW>
-__device__ __forceinline__ void consume_unit(const u32x4* kr, const u32x4* vr, int quarter, int rg, int nvalid,
-                                             const float (&qv)[G][8], float (&m_run)[G], float (&l_run)[G],
-                                             float (&o_acc)[G][8]) {
-    using U = Unit<D, PW>;
-    constexpr int NI = U::NI;
-    float sc[G][NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        float kf[8];
-        bf16x8_to_float(kr[i], kf);
-#pragma unroll
-        for (int e = 0; e < G; ++e) {
-            float acc = 0.f;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) acc = fmaf(qv[e][k], kf[k], acc);
-            sc[e][i] = acc;
-        }
-    }
-#pragma unroll
-    for (int x = 1; x < U::LPR; x <<= 1)
-#pragma unroll
-        for (int e = 0; e < G; ++e)
-#pragma unroll
-            for (int i = 0; i < NI; ++i) sc[e][i] += __shfl_xor(sc[e][i], x);
-    bool valid[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) valid[i] = quarter * U::KPW + i * U::RPI + rg < nvalid;
-#pragma unroll
-    for (int e = 0; e < G; ++e) {
-        float mx = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < NI; ++i) mx = fmaxf(mx, valid[i] ? sc[e][i] : -INFINITY);
-#pragma unroll
-        for (int x = U::LPR; x < 64; x <<= 1) mx = fmaxf(mx, __shfl_xor(mx, x));
-        const float m_new = fmaxf(m_run[e], mx);
-        if (m_new == -INFINITY) continue;  // no visible key for this wave so far
-        const float alpha = exp2f(m_run[e] - m_new);
-        m_run[e] = m_new;
-        l_run[e] *= alpha;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) o_acc[e][k] *= alpha;
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const float pr = valid[i] ? exp2f(sc[e][i] - m_new) : 0.f;
-            l_run[e] += pr;
-            float vf[8];
-            bf16x8_to_float(valid[i] ? vr[i] : u32x4{0u, 0u, 0u, 0u}, vf);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) o_acc[e][k] = fmaf(pr, vf[k], o_acc[e][k]);
-        }
-    }
+// 16 bytes per lane of a page row, to registers or (in lane order) to LDS;
+// non-temporal, for a page row is read once per step.
+constexpr int CPOL_NT = 2;
+__device__ __forceinline__ u32x4 load_row16_nt(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+    return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, CPOL_NT);
+}
+__device__ __forceinline__ void load_lds16_nt(__amdgpu_buffer_rsrc_t r, void* lds_segment, uint32_t voff,
+                                              uint32_t soff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)lds_segment, 16, voff, soff, 0, CPOL_NT);
 }
 
-// The wave's totals (sums over the RPI key rows of each load) into LDS slot
-// red[wave]: max, sum, unnormalised row.
-template <int D, int G>
-__device__ __forceinline__ void wave_totals_to_lds(float (&red)[G][D + 2], int lane, int rg, int cch,
-                                                   float (&m_run)[G], float (&l_run)[G], float (&o_acc)[G][8]) {
-    constexpr int LPR = D / 8;
-#pragma unroll
-    for (int x = LPR; x < 64; x <<= 1)
-#pragma unroll
-        for (int e = 0; e < G; ++e) {
-            l_run[e] += __shfl_xor(l_run[e], x);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) o_acc[e][k] += __shfl_xor(o_acc[e][k], x);
-        }
-    if (rg == 0) {
-#pragma unroll
-        for (int e = 0; e < G; ++e)
-#pragma unroll
-            for (int k = 0; k < 8; ++k) red[e][2 + cch * 8 + k] = o_acc[e][k];
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (int e = 0; e < G; ++e) {
-            red[e][0] = m_run[e];
-            red[e][1] = l_run[e];
-        }
-    }
+// 16-key V^T operands of four d tiles: four transpose reads at constant offset
+// OFF from their lane addresses and the wait for them in one statement (the
+// destinations are written asynchronously).
+template <int OFF>
+__device__ __forceinline__ void read_v_tr(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x2 (&v)[4]) {
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %4 offset:%8\n\tds_read_b64_tr_b16 %1, %5 offset:%8\n\t"
+        "ds_read_b64_tr_b16 %2, %6 offset:%8\n\tds_read_b64_tr_b16 %3, %7 offset:%8\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+        : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "i"(OFF)
+        : "memory");
 }
 
-template <int D, int G>
-__device__ __forceinline__ void load_query(const __bf16* __restrict__ Q, int b, int Hq, int h, int cch,
-                                           float c_log2, float (&qv)[G][8]) {
-#pragma unroll
-    for (int e = 0; e < G; ++e) {
-        const u32x4 w = *reinterpret_cast<const u32x4*>(Q + ((int64_t)b * Hq + h * G + e) * D + cch * 8);
-        bf16x8_to_float(w, qv[e]);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) qv[e][k] *= c_log2;
-    }
+// x combined with the values of the lanes 16, 32 and 48 apart (same column)
+__device__ __forceinline__ float col_max(float x) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return pair_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
 }
-
-template <int G>
-__device__ __forceinline__ void init_running(float (&m_run)[G], float (&l_run)[G], float (&o_acc)[G][8]) {
-#pragma unroll
-    for (int e = 0; e < G; ++e) {
-        m_run[e] = -INFINITY;
-        l_run[e] = 0.f;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) o_acc[e][k] = 0.f;
-    }
+__device__ __forceinline__ float col_sum(float x) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return pair_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 
 template <int D, int G, int PW>
-__global__ __launch_bounds__(DEC_THREADS) void decode_kernel(
+__global__ __launch_bounds__(DEC_THREADS, 4) void decode_kernel(
     const __bf16* __restrict__ Q, const __bf16* __restrict__ Kp, const __bf16* __restrict__ Vp,
     const int32_t* __restrict__ seq_lens, int32_t num_pages, const int32_t* __restrict__ plan,
     int32_t stride, int32_t cap, __bf16* __restrict__ O, float* __restrict__ LSE,
     float* __restrict__ ws, int32_t Hkv, int32_t nsplit, int32_t ppw, float c_log2) {
-    using U = Unit<D, PW>;
-    constexpr int NI = U::NI;
-    constexpr int REC = G * (D + 2);      // floats per partial record
+    using U = Unit<D>;
+    constexpr int KS = U::KS, DT = U::DT, RB = U::RB;
+    constexpr int REC = G * (D + 2);          // floats per partial record
+    constexpr int UPW = PW / 16 / DEC_WAVES;  // units of a page per wave
+    constexpr int GROUPS = 16 / G < 3 ? 16 / G : 3;  // column groups that carry a part
+    constexpr int COLS = GROUPS * G;
+    constexpr int OST = D + 4;                // floats per O column in LDS (conflict-free 16-byte stores)
 
-    __shared__ float red[DEC_WAVES][G][D + 2];
+    // V units (two per wave), then the waves' results
+    constexpr int V_BYTES = DEC_WAVES * 2 * 16 * RB;
+    constexpr int R_BYTES = DEC_WAVES * COLS * (OST + 2) * 4;
+    __shared__ __align__(256) u32x4 lds[(V_BYTES > R_BYTES ? V_BYTES : R_BYTES) / 16 + 1];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int rg = lane / U::LPR;
-    const int cch = lane % U::LPR;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15;
+    const int quad = lane >> 4;
     const int s = blockIdx.x % nsplit;
     const int bh = blockIdx.x / nsplit;
     const int h = bh % Hkv;
@@ -327,40 +261,158 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_kernel(
     const int p0 = s * ppw;
     const int p1 = min(npages, p0 + ppw);
 
-    float qv[G][8];
-    load_query<D, G>(Q, b, Hq, h, cch, c_log2, qv);
-    float m_run[G], l_run[G], o_acc[G][8];
-    init_running<G>(m_run, l_run, o_acc);
-
-    // Wave w takes quarter w of every page of the split; with PREFETCH the
-    // next page's loads are issued before the current page is consumed (where
-    // registers allow), so a wave keeps two pages of loads in flight.  Pages
-    // written by the planner are in range; the clamp only keeps a foreign plan
-    // row from addressing memory outside the cache.
-    constexpr bool PREFETCH = G * NI <= 16;
-    auto page_base = [&](int p) {
-        return ((int64_t)min(max(row[2 + p], 0), num_pages - 1) * Hkv + h) * PW * D;
-    };
-    u32x4 kr[NI], vr[NI];
-    if constexpr (PREFETCH) load_unit<D, PW>(Kp, Vp, page_base(p0), wave, rg, cch, kr, vr);
-    for (int p = p0; p < p1; ++p) {
-        const int nvalid = p < c ? PW : (int)(sv.t - sv.j * PW + 1);
-        u32x4 kn[NI], vn[NI];
-        if constexpr (PREFETCH) {
-            if (p + 1 < p1) load_unit<D, PW>(Kp, Vp, page_base(p + 1), wave, rg, cch, kn, vn);
-        } else {
-            load_unit<D, PW>(Kp, Vp, page_base(p), wave, rg, cch, kr, vr);
-        }
-        consume_unit<D, G, PW>(kr, vr, wave, rg, nvalid, qv, m_run, l_run, o_acc);
-        if constexpr (PREFETCH) {
+    // this wave's LDS: two V units
+    char* vbuf = reinterpret_cast<char*>(&lds[0]) + wave * (2 * 16 * RB);
+    // lane offsets inside a unit: K operand rows, V rows in swizzled lane order
+    const uint32_t koff = (uint32_t)(col * RB + quad * 16);
+    uint32_t voff[U::SEGS];
 #pragma unroll
-            for (int i = 0; i < NI; ++i) {
-                kr[i] = kn[i];
-                vr[i] = vn[i];
+    for (int i = 0; i < U::SEGS; ++i) {
+        const int r = i * (1024 / RB) + lane / (RB / 16), pc = lane % (RB / 16);
+        voff[i] = (uint32_t)(r * RB + 16 * (2 * ((pc >> 1) ^ vslot<D>(r)) + (pc & 1)));
+    }
+    // transpose reads: key row 4 quad + col / 4, dims 16 dt + 4 (col % 4) ..; the
+    // slot's address bits are clear in the rest, so tile dt is this ^ 32 dt
+    static_assert((16 * RB) % 256 == 0 && RB >= 32 * DT, "slot bits must be clear in unit and row addresses");
+    const uint32_t vtr = lds_addr(vbuf) + (4 * quad + (col >> 2)) * RB + 8 * (col & 3) +
+                         32 * vslot<D>(4 * quad + (col >> 2));
+
+    // Q rows as the score product's B operand
+    bf16x8 qf[KS];
+    {
+        const u32x4* src = reinterpret_cast<const u32x4*>(Q + ((int64_t)b * Hq + h * G + col % G) * D);
+#pragma unroll
+        for (int k = 0; k < KS; ++k) qf[k] = __builtin_bit_cast(bf16x8, src[4 * k + quad]);
+    }
+
+    f32x4 acc[DT];
+#pragma unroll
+    for (int t = 0; t < DT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m_run = -INFINITY, l_run = 0.f;
+
+    // Step st of this wave: page p0 + st / UPW, unit wave + 4 (st % UPW).
+    // Pages written by the planner are in range; the clamp only keeps a foreign
+    // plan row from addressing memory outside the cache.
+    const int nsteps = (p1 - p0) * UPW;
+    auto valid_keys = [&](int p) { return p < c ? PW : (int)(sv.t - sv.j * PW + 1); };
+    struct Where {
+        int64_t base;   // element offset of the page slice
+        uint32_t bytes; // its valid keys
+        uint32_t soff;  // the unit in it
+    };
+    auto where = [&](int st) {
+        const int p = p0 + st / UPW;
+        const int page = __builtin_amdgcn_readfirstlane(min(max(row[2 + p], 0), num_pages - 1));
+        return Where{((int64_t)page * Hkv + h) * PW * D, (uint32_t)valid_keys(p) * RB,
+                     (uint32_t)(wave + DEC_WAVES * (st % UPW)) * 16 * RB};
+    };
+    u32x4 kr[KS];
+    auto load_k = [&](const Where& a) {
+        const __amdgpu_buffer_rsrc_t r = head_rsrc(Kp + a.base, a.bytes);
+#pragma unroll
+        for (int k = 0; k < KS; ++k) kr[k] = load_row16_nt(r, koff + 64 * k, a.soff);
+    };
+    auto load_v = [&](const Where& a, int buf) {
+        const __amdgpu_buffer_rsrc_t r = head_rsrc(Vp + a.base, a.bytes);
+#pragma unroll
+        for (int i = 0; i < U::SEGS; ++i) load_lds16_nt(r, vbuf + buf * (16 * RB) + i * 1024, voff[i], a.soff);
+    };
+    // One unit: its K rows are in flight to kr and its V rows to buffer BUF.  The
+    // next unit's V rows are issued before the wait for them, its K rows as soon
+    // as the scores have taken kr.
+    auto step = [&](int st, auto buf_c) {
+        constexpr int BUF = decltype(buf_c)::value;
+        const int p = p0 + st / UPW, un = wave + DEC_WAVES * (st % UPW);
+        const int nv = valid_keys(p) - 16 * un - 4 * quad;  // valid ones among this lane's keys
+        const bool more = st + 1 < nsteps;
+        const Where nx = where(more ? st + 1 : st);
+        if (more) {
+            load_v(nx, BUF ^ 1);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(U::WAIT_NEXT);
+        } else {
+            __builtin_amdgcn_s_waitcnt(VMCNT0);
+        }
+        f32x4 sc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < KS; ++k)
+            sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[k]), qf[k], sc, 0, 0, 0);
+        if (more) load_k(nx);
+        __builtin_amdgcn_sched_barrier(0);
+        float mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            sc[r] = r < nv ? sc[r] * c_log2 : -INFINITY;
+            mx = fmaxf(mx, sc[r]);
+        }
+        const float m_new = fmaxf(m_run, col_max(mx));
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;
+        if (__any(m_new > m_run)) {
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
+            l_run *= alpha;
+#pragma unroll
+            for (int t = 0; t < DT; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[t][r] *= alpha;
+            m_run = m_new;
+        }
+        bf16x4 pb, pb2;  // this column group's part (G = 8: the third part beside)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float pv = __builtin_amdgcn_exp2f(sc[r] - m_use);
+            l_run += pv;
+            const __bf16 p1b = (__bf16)pv;
+            const float r1 = pv - (float)p1b;
+            const __bf16 p2b = (__bf16)r1;
+            const __bf16 p3b = (__bf16)(r1 - (float)p2b);
+            const int part = col / G;
+            if constexpr (GROUPS == 3) {
+                pb[r] = part == 0 ? p1b : part == 1 ? p2b : part == 2 ? p3b : (__bf16)0.f;
+            } else {
+                pb[r] = part == 0 ? p1b : p2b;
+                pb2[r] = part == 0 ? p3b : (__bf16)0.f;
             }
         }
+#pragma unroll
+        for (int t0 = 0; t0 < DT; t0 += 4) {
+            u32x2 vt[4];
+            read_v_tr<BUF * 16 * RB>(vtr ^ (32 * t0), vtr ^ (32 * t0 + 32), vtr ^ (32 * t0 + 64), vtr ^ (32 * t0 + 96),
+                                     vt);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const s16x4 a = __builtin_bit_cast(s16x4, vt[t]);
+                f32x4& o = acc[t0 + t];
+                o = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, __builtin_bit_cast(s16x4, pb), o, 0, 0, 0);
+                if constexpr (GROUPS < 3)
+                    o = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, __builtin_bit_cast(s16x4, pb2), o, 0, 0, 0);
+            }
+        }
+    };
+
+    {
+        const Where w0 = where(0);
+        load_v(w0, 0);
+        load_k(w0);
     }
-    wave_totals_to_lds<D, G>(red[wave], lane, rg, cch, m_run, l_run, o_acc);
+    for (int st = 0; st < nsteps; st += 2) {
+        step(st, std::integral_constant<int, 0>{});
+        if (st + 1 < nsteps) step(st + 1, std::integral_constant<int, 1>{});
+    }
+
+    // ---- the four waves' results through LDS (over the V units) ----------------
+    float* r_o = reinterpret_cast<float*>(&lds[0]);       // [wave][column][OST]
+    float* r_m = r_o + DEC_WAVES * COLS * OST;            // [wave][column][max, sum]
+    l_run = col_sum(l_run);
+    __syncthreads();
+    if (col < COLS) {
+        float* dst = r_o + (wave * COLS + col) * OST + 4 * quad;
+#pragma unroll
+        for (int t = 0; t < DT; ++t) *reinterpret_cast<f32x4*>(dst + 16 * t) = acc[t];
+        if (quad == 0) {
+            r_m[(wave * COLS + col) * 2] = m_run;
+            r_m[(wave * COLS + col) * 2 + 1] = l_run;
+        }
+    }
     __syncthreads();
 
     const bool single = nsb == 1;
@@ -369,13 +421,17 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_kernel(
         const int e = x / D, d = x % D;
         float M = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < DEC_WAVES; ++w) M = fmaxf(M, red[w][e][0]);
+        for (int w = 0; w < DEC_WAVES; ++w) M = fmaxf(M, r_m[(w * COLS + e) * 2]);
         float o = 0.f, l = 0.f;
 #pragma unroll
         for (int w = 0; w < DEC_WAVES; ++w) {
-            const float sw = red[w][e][0] == -INFINITY ? 0.f : exp2f(red[w][e][0] - M);
-            o = fmaf(red[w][e][2 + d], sw, o);
-            l = fmaf(red[w][e][1], sw, l);
+            const float mw = r_m[(w * COLS + e) * 2];
+            const float sw = mw == -INFINITY ? 0.f : exp2f(mw - M);
+            float ow = r_o[(w * COLS + e) * OST + d];
+#pragma unroll
+            for (int gr = 1; gr < GROUPS; ++gr) ow += r_o[(w * COLS + gr * G + e) * OST + d];
+            o = fmaf(ow, sw, o);
+            l = fmaf(r_m[(w * COLS + e) * 2 + 1], sw, l);
         }
         if (single) {
             O[((int64_t)b * Hq + h * G + e) * D + d] = (__bf16)(o / l);
