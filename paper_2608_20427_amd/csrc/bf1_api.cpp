@@ -92,18 +92,44 @@ bool decode_cap(int64_t max_seq_len, int64_t B, int64_t L, bool dense, int64_t* 
     return true;
 }
 
-// Splits per (sequence, kv-head) and pages per split for lists of up to P
-// pages: about 1024 workgroups (four per CU; more or fewer measured no
-// faster for the selected lists and slower for long dense ones), at most 256
-// splits, splits as even as possible.
-void decode_splits(int64_t batch, int64_t Hkv, int64_t P, int32_t* nsplit, int32_t* ppw) {
-    const int64_t units = std::max<int64_t>(1, batch * Hkv);
-    const int64_t want = std::max<int64_t>(1, (1024 + units - 1) / units);
-    int64_t ns = std::min<int64_t>(std::min<int64_t>(P, want), 256);
-    ns = std::max<int64_t>(ns, 1);
+// Pages per split, and the splits that makes, for lists of up to P pages cut
+// into at most `most` splits of equal size.
+void decode_even(int64_t P, int64_t most, int32_t* nsplit, int32_t* ppw) {
+    const int64_t ns = std::max<int64_t>(1, std::min<int64_t>(P, most));
     const int64_t pp = (P + ns - 1) / ns;
     *nsplit = (int32_t)((P + pp - 1) / pp);
     *ppw = (int32_t)pp;
+}
+
+// Splits that a workspace of bf1_decode_workspace_size holds records for.
+int32_t decode_ws_splits(int64_t batch, int64_t Hkv, int64_t P) {
+    const int64_t units = std::max<int64_t>(1, batch * Hkv);
+    int32_t nsplit, ppw;
+    decode_even(P, std::min<int64_t>((1024 + units - 1) / units, 256), &nsplit, &ppw);
+    return nsplit;
+}
+
+// Splits of a step per (sequence, kv-head) and pages per split, never more than
+// decode_ws_splits.  units = sequences x kv-heads.  A selected list is some
+// twelve pages: from 192 units (three quarters of the compute units) it is not
+// cut, which also saves the merge launch; up to 64 units it is cut for one
+// workgroup per compute unit, in between for four.  A long (dense) list is cut
+// for four workgroups per compute unit into at most 32, two rounds of the merge.
+// Device time of a step at 32K tokens, 16/8 heads of 128, us, uncut / 4 splits /
+// finest: 64 units 15.4 / 11.7 / 11.5, 128 17.1 / 15.4 / 15.3, 160 18.2 / 18.4 /
+// 17.4, 224 19.2 / 22.2 / 22.1, 256 19.8 / 23.2 / 23.2, 384 29.3 / 31.2 / 30.9;
+// 16/2 heads, 64 units 16.8 / 17.9 / 18.9; one dense list 40 with 128 splits, 31
+// with 32.
+void decode_splits(int64_t batch, int64_t Hkv, int64_t P, int32_t* nsplit, int32_t* ppw) {
+    const int64_t units = std::max<int64_t>(1, batch * Hkv);
+    int64_t want = (1024 + units - 1) / units;
+    if (P > 16)
+        want = std::min<int64_t>(want, 32);
+    else if (units >= 192)
+        want = 1;
+    else if (units <= 64)
+        want = std::max<int64_t>(4, (256 + units - 1) / units);
+    decode_even(P, want, nsplit, ppw);
 }
 
 int64_t decode_ws_bytes(int64_t batch, int64_t Hq, int64_t Hkv, int64_t D, int64_t nsplit) {
@@ -654,9 +680,7 @@ int bf1_decode_workspace_size(int32_t batch, int32_t Hq, int32_t Hkv, int32_t he
     if (!bytes || batch < 0 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0 || plan_stride < 3)
         return BF1_ERR_INVALID_ARG;
     if (head_dim != 64 && head_dim != 128) return BF1_ERR_UNSUPPORTED;
-    int32_t nsplit, ppw;
-    decode_splits(batch, Hkv, (int64_t)plan_stride - 2, &nsplit, &ppw);
-    *bytes = decode_ws_bytes(batch, Hq, Hkv, head_dim, nsplit);
+    *bytes = decode_ws_bytes(batch, Hq, Hkv, head_dim, decode_ws_splits(batch, Hkv, (int64_t)plan_stride - 2));
     return BF1_OK;
 }
 
@@ -678,9 +702,11 @@ int bf1_decode_attn(const void* Q, const void* K_pages, const void* V_pages, con
         !aligned(workspace, 16) || !aligned(seq_lens, 4) || !aligned(plan, 4))
         return BF1_ERR_INVALID_ARG;
     if (LSE && !aligned(LSE, 4)) return BF1_ERR_INVALID_ARG;
+    const int64_t P = (int64_t)plan_stride - 2;
+    if (workspace_bytes < decode_ws_bytes(batch, Hq, Hkv, head_dim, decode_ws_splits(batch, Hkv, P)))
+        return BF1_ERR_BUFFER_TOO_SMALL;
     int32_t nsplit, ppw;
-    decode_splits(batch, Hkv, (int64_t)plan_stride - 2, &nsplit, &ppw);
-    if (workspace_bytes < decode_ws_bytes(batch, Hq, Hkv, head_dim, nsplit)) return BF1_ERR_BUFFER_TOO_SMALL;
+    decode_splits(batch, Hkv, P, &nsplit, &ppw);
     bf1::DecodeArgs a{Q, K_pages, V_pages, seq_lens, num_pages, plan, plan_stride, plan_stride - 3, O,
                       LSE, (float*)workspace, batch, Hq, Hkv, head_dim, B, nsplit, ppw};
     return status_of(bf1::launch_decode(a, (hipStream_t)stream));
