@@ -4,7 +4,7 @@
 // and the SwiGLU product).
 //
 // All of them are bound by memory: each activation is read once and written
-// once, 16 (or two times 8) bytes per lane, where a chain of one-operation
+// once, 16 bytes per lane, where a chain of one-operation
 // kernels moves it some ten times and pays a launch each.  Arithmetic is fp32
 // and every value is rounded to bf16 exactly where the operator-by-operator
 // form rounds it (after the residual add, after each norm, after the rotary
@@ -26,14 +26,6 @@ constexpr int ROW_THREADS = 256;
 __device__ __forceinline__ void unpack8(u32x4 w, float* f) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        f[2 * k] = __uint_as_float(w[k] << 16);
-        f[2 * k + 1] = __uint_as_float(w[k] & 0xffff0000u);
-    }
-}
-
-__device__ __forceinline__ void unpack4(u32x2 w, float* f) {
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
         f[2 * k] = __uint_as_float(w[k] << 16);
         f[2 * k + 1] = __uint_as_float(w[k] & 0xffff0000u);
     }
@@ -107,18 +99,19 @@ __global__ __launch_bounds__(ROW_THREADS) void rms_kernel(__bf16* __restrict__ h
 // ---------------------------------------------------------------------------
 // q [n, H D], k and v [n, Hkv D] (row strides ldq, ldk, ldv) into head-major
 // Q [H, n, D], K, V [Hkv, n, D]; Q and K rows get their RMSNorm and rotary
-// embedding on the way (cos, sin: fp32 [n, D], their two halves equal).  D / 8
-// lanes per (token, head) row; a lane owns 4 elements of the lower half of the
-// row and the 4 they are rotated with, so the rotation stays in the lane.
-// 8192 tokens of 16 + 2 * 8 heads of 128: 32 us for 142 MB (4.4 TB/s), some
-// 420 as single operators (norms, rotations and three transposed copies).
+// embedding on the way (cos, sin: fp32 [n, D], their two halves equal).  D / 16
+// lanes per (token, head) row; a lane owns 8 elements of the lower half of the
+// row and the 8 they are rotated with, so the rotation stays in the lane.
+// 8192 tokens of 16 + 2 * 8 heads of 128: 26 us for 142 MB (5.5 TB/s; 32 us with
+// 8-byte loads and D / 8 lanes per row), some 420 as single operators (norms,
+// rotations and three transposed copies).
 template <int D>
 __global__ __launch_bounds__(ROW_THREADS) void heads_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v, int64_t ldq,
     int64_t ldk, int64_t ldv, const __bf16* __restrict__ qgain, const __bf16* __restrict__ kgain,
     const float* __restrict__ cosv, const float* __restrict__ sinv, __bf16* __restrict__ Q, __bf16* __restrict__ K,
     __bf16* __restrict__ V, int32_t n, int32_t H, int32_t Hkv, float eps) {
-    constexpr int LPR = D / 8;
+    constexpr int LPR = D / 16;
     constexpr int RPB = ROW_THREADS / LPR;
     const int32_t heads = H + 2 * Hkv;
     const int64_t p = (int64_t)blockIdx.x * RPB + threadIdx.x / LPR;
@@ -142,35 +135,36 @@ __global__ __launch_bounds__(ROW_THREADS) void heads_kernel(
         dst = V + ((int64_t)(hd - H - Hkv) * n + tok) * D;
         gain = nullptr;
     }
-    u32x2 lo = reinterpret_cast<const u32x2*>(src)[l];
-    u32x2 hi = reinterpret_cast<const u32x2*>(src + D / 2)[l];
-    float a[4], b[4], s = 0.f;
-    unpack4(lo, a);
-    unpack4(hi, b);
+    u32x4 lo = reinterpret_cast<const u32x4*>(src)[l];
+    u32x4 hi = reinterpret_cast<const u32x4*>(src + D / 2)[l];
+    float a[8], b[8], s = 0.f;
+    unpack8(lo, a);
+    unpack8(hi, b);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s += a[e] * a[e] + b[e] * b[e];
+    for (int e = 0; e < 8; ++e) s += a[e] * a[e] + b[e] * b[e];
 #pragma unroll
     for (int m = LPR / 2; m > 0; m >>= 1) s += __shfl_xor(s, m);
     if (!live) return;
     if (gain != nullptr) {
         const float rs = 1.0f / sqrtf(s / (float)D + eps);
-        float ga[4], gb[4];
-        unpack4(reinterpret_cast<const u32x2*>(gain)[l], ga);
-        unpack4(reinterpret_cast<const u32x2*>(gain + D / 2)[l], gb);
-        const f32x4 c = reinterpret_cast<const f32x4*>(cosv + (int64_t)tok * D)[l];
-        const f32x4 t = reinterpret_cast<const f32x4*>(sinv + (int64_t)tok * D)[l];
-        bf16x4 ya, yb;
+        float ga[8], gb[8];
+        unpack8(reinterpret_cast<const u32x4*>(gain)[l], ga);
+        unpack8(reinterpret_cast<const u32x4*>(gain + D / 2)[l], gb);
+        const f32x4* cp = reinterpret_cast<const f32x4*>(cosv + (int64_t)tok * D) + 2 * l;
+        const f32x4* tp = reinterpret_cast<const f32x4*>(sinv + (int64_t)tok * D) + 2 * l;
+        const f32x4 c[2] = {cp[0], cp[1]}, t[2] = {tp[0], tp[1]};
+        float ya[8], yb[8];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
+        for (int e = 0; e < 8; ++e) {
             const float na = (float)(__bf16)(a[e] * rs * ga[e]), nb = (float)(__bf16)(b[e] * rs * gb[e]);
-            ya[e] = (__bf16)(na * c[e] - nb * t[e]);
-            yb[e] = (__bf16)(nb * c[e] + na * t[e]);
+            ya[e] = na * c[e >> 2][e & 3] - nb * t[e >> 2][e & 3];
+            yb[e] = nb * c[e >> 2][e & 3] + na * t[e >> 2][e & 3];
         }
-        lo = __builtin_bit_cast(u32x2, ya);
-        hi = __builtin_bit_cast(u32x2, yb);
+        lo = pack8(ya);
+        hi = pack8(yb);
     }
-    reinterpret_cast<u32x2*>(dst)[l] = lo;
-    reinterpret_cast<u32x2*>(dst + D / 2)[l] = hi;
+    reinterpret_cast<u32x4*>(dst)[l] = lo;
+    reinterpret_cast<u32x4*>(dst + D / 2)[l] = hi;
 }
 
 // ---------------------------------------------------------------------------
@@ -242,7 +236,7 @@ int bf1_stack_heads(const void* q, const void* k, const void* v, int64_t ldq, in
         ldk % 8 || ldv % 8)
         return BF1_ERR_INVALID_ARG;
     const int64_t rows = n * (H + 2 * (int64_t)Hkv);
-    const int rpb = bf1::ROW_THREADS / (head_dim / 8);
+    const int rpb = bf1::ROW_THREADS / (head_dim / 16);
     const int64_t grid = (rows + rpb - 1) / rpb;
     if (grid > 0x7fffffff) return BF1_ERR_UNSUPPORTED;
     auto launch = [&](auto kern) {

@@ -163,6 +163,11 @@ class PrefillStack:
                 return False
         return True
 
+    def _plain_gain(self, t, h):
+        """Whether norm gain t suits the norm kernel for rows of h."""
+        return t.shape == h.shape[1:] and t.dtype == torch.bfloat16 and t.device == h.device and t.is_contiguous() \
+            and t.data_ptr() % 16 == 0 and not (torch.is_grad_enabled() and t.requires_grad)
+
     def _rms_fused(self, h, r, gain):
         """h <- h + r in place (if r is given), then RMSNorm(h) * gain."""
         out = torch.empty_like(h)
@@ -212,6 +217,10 @@ class PrefillStack:
                     continue
                 h, r = h if r is None else h + r, None
                 h = self._layer_plain(l, h, cos, sin, bf1_layers, dense_attention)
-        last = h[-1:] if r is None else h[-1:] + r[-1:]
-        last = self._rms(last, w["final_norm"])
+            last = h[-1:]
+            gain = w["final_norm"]
+            if r is not None and self._plain_gain(gain, h):
+                last = self._rms_fused(last, r[-1:], gain)  # h's last row is not read again
+            else:
+                last = self._rms(last if r is None else last + r[-1:], gain)
         return (last @ w["embed"].t()).float()[0]
