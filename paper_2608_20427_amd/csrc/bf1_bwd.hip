@@ -602,27 +602,24 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(
     const int key = e / BD, d = e % BD;
     const int32_t kp = i * BW + u * KT + key;
     const float* pk = part + ((int64_t)bh * nslots + s0) * SLOT + e;
-    // the first segment's sums are in dK and dV already; slots are added in
-    // order, eight slots' loads issued before their sums
+    // The first segment's sums are in dK and dV already; slots are added in
+    // order, eight slots' loads issued before their sums (a slot past the last
+    // adds zero).  A loop of single slots for the remainder cost one round trip
+    // to memory each: 32K tokens, 31 slots, 9.2 us against 7.1.
     const int64_t at = (kvrow0 + kp) * BD + d;
     float sk = kp < n ? dK[at] : 0.f, sv = kp < n ? dV[at] : 0.f;
-    int32_t s = 0;
-    for (; s + 8 <= ns; s += 8) {
+    for (int32_t s = 0; s < ns; s += 8) {
         float kk[8], vv[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            kk[q] = pk[(s + q) * SLOT];
-            vv[q] = pk[(s + q) * SLOT + KT * BD];
+            kk[q] = s + q < ns ? pk[(s + q) * SLOT] : 0.f;
+            vv[q] = s + q < ns ? pk[(s + q) * SLOT + KT * BD] : 0.f;
         }
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             sk += kk[q];
             sv += vv[q];
         }
-    }
-    for (; s < ns; ++s) {
-        sk += pk[s * SLOT];
-        sv += pk[s * SLOT + KT * BD];
     }
     if (kp < n) {
         dK[at] = sk;
