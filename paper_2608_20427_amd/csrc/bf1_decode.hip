@@ -50,6 +50,7 @@ namespace {
 constexpr int DEC_THREADS = 256;
 constexpr int DEC_WAVES = DEC_THREADS / 64;
 constexpr int PLAN_THREADS = 64;
+constexpr float MIN_PART = 0x1p-132f;  // least first part of a weight: its half is the smallest bf16 number
 constexpr int MAX_ROUTE = 64;  // bound on |P(j)| - 1 for any j < 2^31 and L <= 32
 
 // ---------------------------------------------------------------------------
@@ -152,9 +153,12 @@ __device__ __forceinline__ void write_nan(__bf16* O, float* LSE, int b, int Hq, 
 // keys 4 (l / 16) + 0..3 and column l % 16, which is the B operand of
 // O^T += V^T P^T as it stands.  That product needs 16-bit weights, so a weight
 // goes in as three bf16 parts that add up to the fp32 value (each part the
-// rounded rest of the ones before: 24 bits), one part per column group; the
-// epilogue adds the groups' columns.  G = 8 has two column groups; the third
-// part takes a second product.  V^T comes from LDS by transpose reads: a V unit
+// rounded rest of the ones before: 24 bits), one part per column group.  G = 8
+// has two column groups and a second product: the first group takes the first
+// part in two halves, the other the second and the third part.  The rests are
+// often zero or negative, so an infinite value would make NaN of them: the first
+// group's columns never meet a rest, and the epilogue adds the other columns
+// only where the first is finite.  V^T comes from LDS by transpose reads: a V unit
 // is staged by direct buffer -> LDS loads, 32-byte slot s of key row r at
 // s ^ vslot(r) (conflict-free: the 16 rows of a read hit distinct banks).
 // Rows past the valid keys are zeros by the buffer range check, whatever the
@@ -348,7 +352,7 @@ __global__ __launch_bounds__(DEC_THREADS, 4) void decode_kernel(
         const float m_new = fmaxf(m_run, col_max(mx));
         const float m_use = m_new == -INFINITY ? 0.f : m_new;
         if (__any(m_new > m_run)) {
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
+            const float alpha = exp2f(m_run - m_use);
             l_run *= alpha;
 #pragma unroll
             for (int t = 0; t < DT; ++t)
@@ -356,12 +360,29 @@ __global__ __launch_bounds__(DEC_THREADS, 4) void decode_kernel(
                 for (int r = 0; r < 4; ++r) acc[t][r] *= alpha;
             m_run = m_new;
         }
-        bf16x4 pb, pb2;  // this column group's part (G = 8: the third part beside)
+        bf16x4 pb, pb2;  // this column group's parts in the first product, and (G = 8) in the second
+        // Weights and what their first parts are made of.  The exp2 instruction
+        // gives 0 below 2^-126: weights there take the library function and a first
+        // part above 0, so that an infinite value counts at every weight fp32 holds.
+        // Asking costs a step 0.5% with heads of 128, 1.5% with heads of 64.
+        float w[4], first[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w[r] = sc[r] - m_use;
+        if (__builtin_expect(__any(fminf(fminf(w[0], w[1]), fminf(w[2], w[3])) < -126.f), 0)) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                w[r] = exp2f(w[r]);
+                first[r] = w[r] > 0.f ? fmaxf(w[r], MIN_PART) : w[r];
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) first[r] = w[r] = __builtin_amdgcn_exp2f(w[r]);
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const float pv = __builtin_amdgcn_exp2f(sc[r] - m_use);
+            const float pv = w[r];
             l_run += pv;
-            const __bf16 p1b = (__bf16)pv;
+            const __bf16 p1b = (__bf16)first[r];
             const float r1 = pv - (float)p1b;
             const __bf16 p2b = (__bf16)r1;
             const __bf16 p3b = (__bf16)(r1 - (float)p2b);
@@ -369,8 +390,9 @@ __global__ __launch_bounds__(DEC_THREADS, 4) void decode_kernel(
             if constexpr (GROUPS == 3) {
                 pb[r] = part == 0 ? p1b : part == 1 ? p2b : part == 2 ? p3b : (__bf16)0.f;
             } else {
-                pb[r] = part == 0 ? p1b : p2b;
-                pb2[r] = part == 0 ? p3b : (__bf16)0.f;
+                const __bf16 half1 = (__bf16)(0.5f * (float)p1b);
+                pb[r] = part == 0 ? half1 : p2b;
+                pb2[r] = part == 0 ? half1 : p3b;
             }
         }
 #pragma unroll
@@ -427,9 +449,10 @@ __global__ __launch_bounds__(DEC_THREADS, 4) void decode_kernel(
         for (int w = 0; w < DEC_WAVES; ++w) {
             const float mw = r_m[(w * COLS + e) * 2];
             const float sw = mw == -INFINITY ? 0.f : exp2f(mw - M);
-            float ow = r_o[(w * COLS + e) * OST + d];
+            float ow = r_o[(w * COLS + e) * OST + d], rest = 0.f;
 #pragma unroll
-            for (int gr = 1; gr < GROUPS; ++gr) ow += r_o[(w * COLS + gr * G + e) * OST + d];
+            for (int gr = 1; gr < GROUPS; ++gr) rest += r_o[(w * COLS + gr * G + e) * OST + d];
+            ow = fabsf(ow) < INFINITY ? ow + rest : ow;
             o = fmaf(ow, sw, o);
             l = fmaf(r_m[(w * COLS + e) * 2 + 1], sw, l);
         }
