@@ -92,44 +92,65 @@ bool decode_cap(int64_t max_seq_len, int64_t B, int64_t L, bool dense, int64_t* 
     return true;
 }
 
-// Pages per split, and the splits that makes, for lists of up to P pages cut
-// into at most `most` splits of equal size.
-void decode_even(int64_t P, int64_t most, int32_t* nsplit, int32_t* ppw) {
-    const int64_t ns = std::max<int64_t>(1, std::min<int64_t>(P, most));
-    const int64_t pp = (P + ns - 1) / ns;
-    *nsplit = (int32_t)((P + pp - 1) / pp);
-    *ppw = (int32_t)pp;
+// Splits that a workspace of bf1_decode_workspace_size holds records for: lists
+// of up to P pages cut for about 1024 workgroups, at most 256, of equal size.
+int64_t decode_ws_splits(int64_t batch, int64_t Hkv, int64_t P) {
+    const int64_t units = std::max<int64_t>(1, batch * Hkv);
+    const int64_t most = std::min<int64_t>(P, std::min<int64_t>((1024 + units - 1) / units, 256));
+    const int64_t pages = (P + most - 1) / most;
+    return (P + pages - 1) / pages;
 }
 
-// Splits that a workspace of bf1_decode_workspace_size holds records for.
-int32_t decode_ws_splits(int64_t batch, int64_t Hkv, int64_t P) {
+// Most splits of a step per (sequence, kv-head), never more than
+// decode_ws_splits, and pages per split.  units = sequences x kv-heads, for 256
+// compute units that hold four workgroups each.  Device time of a step, us, by
+// splits:
+//
+// Lists of up to 16 pages (the selected ones) are walked uncut from a number of
+// units on that depends on the instance: an uncut list is a chain of its pages,
+// a cut one pays the merge launch, which costs more for more q-heads, while the
+// bytes (half with heads of 64) come in at the same rate.  32K tokens, uncut / 2 /
+// finest: heads of 128, pages of 64, one q-head: 128 units 17.6 / 15.8 / 15.4, 192
+// 18.5 / 21.6 / 19.8, 256 19.4 / 22.5 / 23.0; four: 128 18.1 / 17.8 / 18.2, 160
+// 18.6 / 22.6 / 20.4; eight: 64 18.0 / 20.3 / 18.6, 96 18.1 / 20.7 / 22.0, 128 18.5 /
+// 21.3 / 22.1.  Pages of 128, one q-head: 192 30.1 / 30.2 / 28.3, 256 32.0 / 33.5 /
+// 36.4; eight: 128 29.6 / 27.7 / 29.0, 192 30.9 / 36.1 / 35.1.  Heads of 64, pages of
+// 64, one: 192 15.3 / 14.5 / 13.6, 256 15.5 / 15.2 / 15.7, 384 17.7 / 18.7 / 20.0;
+// eight: 128 14.8 / 15.0 / 14.3, 192 14.8 / 16.7 / 16.4.  Pages of 128, one: 256 25.0 /
+// 20.9 / 22.8, 384 28.3 / 27.5 / 30.0, 512 30.7 / 34.4 / 34.0; eight: 256 24.0 / 23.3 /
+// 25.1, 320 27.9 / 28.6 / 29.6.  Below that line two splits from 193 units on, the
+// finest cut before; up to 64 units at most 16 splits, one round of the merge, or
+// where a merge thread has two or more outputs, some four per compute unit.
+//
+// Longer lists (dense ones) are cut for four workgroups per compute unit into at
+// most 32 splits, or for one per compute unit (two with heads of 64) where that
+// makes more, and above 32 pages into no more rounds than decode_rounds (its
+// comment has the figures; 24 pages of 128 tokens, 10.6 with 24 splits, 11.6 with
+// 12): 16/8 heads of 128, 1024 pages, 4 units 48.0 / 35.0 / 40.5 with 32 / 64 / 128,
+// 8 units 51.8 / 53.3 with 32 / 64, 16 units 92.2 / 88.2 / 93.3 with 16 / 32 / 64; heads of
+// 64, 8 units 39.6 / 33.4 / 40.3 with 32 / 64 / 128.  A list in a row for more than 32
+// pages is cut by its own length (ppw 0, decode_pages_per_split).
+void decode_splits(int64_t batch, int64_t Hkv, int64_t G, int64_t D, int64_t B, int64_t P, int32_t* nsplit,
+                   int32_t* ppw) {
+    // by head size, page width and q-heads per kv-head (1, 2, 4, 8)
+    static constexpr int uncut_from[2][2][4] = {{{256, 256, 256, 192}, {448, 448, 448, 320}},
+                                                {{192, 192, 160, 96}, {256, 256, 192, 192}}};
     const int64_t units = std::max<int64_t>(1, batch * Hkv);
-    int32_t nsplit, ppw;
-    decode_even(P, std::min<int64_t>((1024 + units - 1) / units, 256), &nsplit, &ppw);
-    return nsplit;
-}
-
-// Splits of a step per (sequence, kv-head) and pages per split, never more than
-// decode_ws_splits.  units = sequences x kv-heads.  A selected list is some
-// twelve pages: from 192 units (three quarters of the compute units) it is not
-// cut, which also saves the merge launch; up to 64 units it is cut for one
-// workgroup per compute unit, in between for four.  A long (dense) list is cut
-// for four workgroups per compute unit into at most 32, two rounds of the merge.
-// Device time of a step at 32K tokens, 16/8 heads of 128, us, uncut / 4 splits /
-// finest: 64 units 15.4 / 11.7 / 11.5, 128 17.1 / 15.4 / 15.3, 160 18.2 / 18.4 /
-// 17.4, 224 19.2 / 22.2 / 22.1, 256 19.8 / 23.2 / 23.2, 384 29.3 / 31.2 / 30.9;
-// 16/2 heads, 64 units 16.8 / 17.9 / 18.9; one dense list 40 with 128 splits, 31
-// with 32.
-void decode_splits(int64_t batch, int64_t Hkv, int64_t P, int32_t* nsplit, int32_t* ppw) {
-    const int64_t units = std::max<int64_t>(1, batch * Hkv);
+    const int64_t outs = (G * D + 255) / 256;
     int64_t want = (1024 + units - 1) / units;
-    if (P > 16)
-        want = std::min<int64_t>(want, 32);
-    else if (units >= 192)
+    if (P > 16) {
+        const int64_t fill = ((D == 64 ? 512 : 256) + units - 1) / units;
+        want = std::max(std::min<int64_t>(want, 32), fill);
+        if (P > 32) want = std::min<int64_t>(want, 16 * bf1::decode_rounds((int32_t)P, (int32_t)outs, 256));
+    } else if (units >= uncut_from[D == 128][B == 128][G == 8 ? 3 : G / 2]) {
         want = 1;
-    else if (units <= 64)
-        want = std::max<int64_t>(4, (256 + units - 1) / units);
-    decode_even(P, want, nsplit, ppw);
+    } else if (units > 192) {
+        want = 2;
+    } else if (units <= 64) {
+        want = outs == 1 ? 16 : std::max<int64_t>(4, (256 + units - 1) / units);
+    }
+    *nsplit = (int32_t)std::min(want, decode_ws_splits(batch, Hkv, P));
+    *ppw = P > 32 ? 0 : (int32_t)((P + *nsplit - 1) / *nsplit);
 }
 
 int64_t decode_ws_bytes(int64_t batch, int64_t Hq, int64_t Hkv, int64_t D, int64_t nsplit) {
@@ -706,7 +727,7 @@ int bf1_decode_attn(const void* Q, const void* K_pages, const void* V_pages, con
     if (workspace_bytes < decode_ws_bytes(batch, Hq, Hkv, head_dim, decode_ws_splits(batch, Hkv, P)))
         return BF1_ERR_BUFFER_TOO_SMALL;
     int32_t nsplit, ppw;
-    decode_splits(batch, Hkv, P, &nsplit, &ppw);
+    decode_splits(batch, Hkv, G, head_dim, B, P, &nsplit, &ppw);
     bf1::DecodeArgs a{Q, K_pages, V_pages, seq_lens, num_pages, plan, plan_stride, plan_stride - 3, O,
                       LSE, (float*)workspace, batch, Hq, Hkv, head_dim, B, nsplit, ppw};
     return status_of(bf1::launch_decode(a, (hipStream_t)stream));

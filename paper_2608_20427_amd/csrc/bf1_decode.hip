@@ -26,8 +26,8 @@
 // a split is `ppw` consecutive pages of the sequence's list (earlier pages,
 // then the self page).  Each wave takes 16 keys of every 64 as one matrix tile
 // and keeps an online softmax (log2 units).  The four waves merge in LDS; a
-// split that covers the
-// whole list writes O and LSE at once, otherwise it writes a partial record
+// split that covers the whole list writes O and LSE at once, otherwise it
+// writes a partial record
 // (per q-head: max, sum, unnormalised O row).  Merge kernel: one workgroup
 // per (sequence, kv-head) with more than one split sums the records in split
 // order (deterministic).  The kernel boundary orders the records before their
@@ -115,6 +115,9 @@ __global__ __launch_bounds__(PLAN_THREADS) void decode_plan_kernel(
 // ---------------------------------------------------------------------------
 // Decode attention.
 // ---------------------------------------------------------------------------
+
+template <int D, int G>
+constexpr int MERGE_OUTS = (G * D + DEC_THREADS - 1) / DEC_THREADS;  // outputs of a merge thread
 
 // What one step of sequence b reads: its newest position t, block j and the
 // number c of earlier pages in its plan row.  False if the plan row was made
@@ -260,6 +263,7 @@ __global__ __launch_bounds__(DEC_THREADS, 4) void decode_kernel(
     }
     const int c = sv.c;
     const int npages = c + 1;
+    if (ppw == 0) ppw = decode_pages_per_split(npages, MERGE_OUTS<D, G>, nsplit);
     const int nsb = (npages + ppw - 1) / ppw;
     if (s >= nsb) return;
     const int p0 = s * ppw;
@@ -479,7 +483,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_merge_kernel(
     int32_t cap, __bf16* __restrict__ O, float* __restrict__ LSE, const float* __restrict__ ws,
     int32_t Hkv, int32_t nsplit, int32_t ppw) {
     constexpr int REC = G * (D + 2);
-    constexpr int U = 16;
+    constexpr int U = 16;  // decode_rounds counts in these
     const int tid = threadIdx.x;
     const int bh = blockIdx.x;
     const int h = bh % Hkv;
@@ -488,7 +492,8 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_merge_kernel(
     StepView sv;
     if (!step_view(seq_lens, plan + (int64_t)b * stride, cap, PW, b, &sv))
         return;  // the split kernel wrote NaN
-    const int nsb = (sv.c + 1 + ppw - 1) / ppw;
+    if (ppw == 0) ppw = decode_pages_per_split(sv.c + 1, MERGE_OUTS<D, G>, nsplit);
+    const int nsb = (sv.c + ppw) / ppw;
     if (nsb <= 1) return;  // the split kernel wrote the result
     const float* recs = ws + (int64_t)bh * nsplit * REC;
     for (int x = tid; x < G * D; x += DEC_THREADS) {

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/bf1.h"
+#include "../../paper_2608_20427_amd/csrc/bf1_kernels.h"
 #include "hip_stubs.h"
 
 static int g_failures = 0;
@@ -183,6 +184,51 @@ static void plan_cache_and_capture() {
     std::printf("allocations %ld frees %ld\n", g_stub.mallocs, g_stub.frees);
 }
 
+// Splits of decode steps: the records always fit the workspace, also for lists
+// shorter than their rows could hold; a long list of few kv-heads fills the
+// chip whatever its row could hold; uncut lists where the merge costs more.
+static int64_t per_split(int64_t pages, int32_t outs) {
+    return g_stub.ppw ? g_stub.ppw : bf1::decode_pages_per_split((int32_t)pages, outs, g_stub.nsplit);
+}
+static int32_t splits(int batch, int Hkv, int G, int D, int B, int64_t pages) {
+    int32_t* ip = reinterpret_cast<int32_t*>(P);
+    int64_t ws = 0;
+    const int32_t stride = (int32_t)pages + 2;
+    CHECK(bf1_decode_workspace_size(batch, G * Hkv, Hkv, D, stride, &ws) == BF1_OK);
+    CHECK(bf1_decode_attn(P, P, P, ip, 8, ip, stride, P, PF, batch, G * Hkv, Hkv, D, B, P, ws - 1, nullptr) ==
+          BF1_ERR_BUFFER_TOO_SMALL);
+    CHECK(bf1_decode_attn(P, P, P, ip, 8, ip, stride, P, PF, batch, G * Hkv, Hkv, D, B, P, ws, nullptr) == BF1_OK);
+    CHECK(g_stub.nsplit >= 1 && g_stub.nsplit <= 256);
+    CHECK((int64_t)batch * Hkv * g_stub.nsplit * G * (D + 2) * 4 <= ws);
+    return g_stub.nsplit;
+}
+
+static void decode_splits() {
+    g_stub = StubState{};
+    for (int G : {1, 2, 4, 8})
+        for (int D : {64, 128})
+            for (int B : {64, 128})
+                for (int64_t pages : {1, 2, 5, 12, 16, 17, 33, 47, 256, 1024, 2048, 262144})
+                    for (int units : {1, 2, 4, 8, 31, 32, 64, 65, 128, 192, 193, 256, 300, 512, 1024, 5000}) {
+                        const int32_t most = splits(units, 1, G, D, B, pages);
+                        const int32_t outs = (G * D + 255) / 256;
+                        // lists up to the row's length: every page in a split, never more splits than records
+                        for (int64_t m : {int64_t(1), int64_t(2), pages / 7 + 1, pages / 2 + 1, pages}) {
+                            if (m > pages) continue;
+                            const int64_t per = per_split(m, outs);
+                            CHECK(per >= 1 && per * most >= m && (m + per - 1) / per <= most);
+                        }
+                    }
+    // one 64K dense list, pages of 64: at most 16 pages in a row on few kv-heads
+    for (int units : {1, 2, 4}) CHECK(splits(units, 1, 2, 128, 64, 1024) > 32 && per_split(1024, 1) <= 16);
+    CHECK(splits(1, 1, 8, 128, 64, 1024) > 32 && per_split(1024, 4) <= 16);
+    // the same 128 pages in a row that could hold 2048
+    for (int units : {1, 2, 8, 32}) CHECK(splits(units, 1, 2, 128, 64, 2048) > 1 && per_split(128, 1) <= 8);
+    // selected lists: finest on few units, uncut on many, the line by the instance
+    CHECK(splits(8, 8, 1, 64, 128, 11) == 11 && splits(24, 8, 1, 64, 128, 11) > 1 && splits(64, 8, 1, 64, 128, 11) == 1);
+    CHECK(splits(16, 8, 2, 128, 64, 12) > 1 && splits(16, 8, 8, 128, 64, 12) == 1 && splits(24, 8, 2, 128, 64, 12) == 1);
+}
+
 int main() {
     const long cases[][3] = {{0, 64, 2}, {1, 64, 2}, {257, 64, 2}, {512, 64, 1}, {4096, 64, 2},
                              {30001, 64, 2}, {1500, 128, 2}, {777, 5, 0}, {20000, 16, 3}, {700, 64, 9}};
@@ -191,6 +237,7 @@ int main() {
     sizes();
     runtime_errors_map_to_bf1_err_hip();
     plan_cache_and_capture();
+    decode_splits();
     std::printf(g_failures == 0 ? "ALL OK\n" : "FAILURES %d\n", g_failures);
     return g_failures == 0 ? 0 : 1;
 }

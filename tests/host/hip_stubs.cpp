@@ -79,8 +79,11 @@ hipError_t launch_backward(const BwdArgs& a, hipStream_t) {
 hipError_t launch_decode_plan(const DecodePlanArgs&, hipStream_t) {
     return g_stub.fail ? hipErrorLaunchFailure : hipSuccess;
 }
-hipError_t launch_decode(const DecodeArgs&, hipStream_t) {
-    return g_stub.fail ? hipErrorLaunchFailure : hipSuccess;
+hipError_t launch_decode(const DecodeArgs& a, hipStream_t) {
+    if (g_stub.fail) return hipErrorLaunchFailure;
+    g_stub.nsplit = a.nsplit;
+    g_stub.ppw = a.ppw;
+    return hipSuccess;
 }
 hipError_t noalloc_scratch(int32_t** ptr) {
     if (g_stub.fail) return hipErrorInvalidSymbol;

@@ -21,14 +21,14 @@ pytestmark = pytest.mark.gpu
 EDGES = [1, 15, 16, 17, 48, 49, 63, 64, 65, 80, 127, 128, 129, 200]
 
 
-def _check(lens, Hq, Hkv, d, B, L, dense, seed):
+def _check(lens, Hq, Hkv, d, B, L, dense, seed, row=0):
     lens = np.asarray(lens, dtype=np.int32)
     w = synth.DecodeWorkload("units", len(lens), int(lens.max()), Hq, Hkv, d, B, L, seed=seed)
     q, k, v, sl = synth.make_decode_host(w, lens)
     q = q * 3                                   # peaked rows as well as flat ones
     kp, vp, table, pages = synth.page_cache(k, v, sl, B, seed)
     dev = torch.from_numpy(sl).cuda()
-    stride = bf1.decode_plan_stride(int(lens.max()), B, L, dense)
+    stride = bf1.decode_plan_stride(max(row, int(lens.max())), B, L, dense)
     plan = bf1.decode_plan(dev, table.cuda(), pages, stride, B, L, dense)
     need = bf1.decode_workspace_size(len(lens), Hq, Hkv, d, stride)
     ws = torch.full((max(16, need),), 255, dtype=torch.uint8, device="cuda")
@@ -50,13 +50,24 @@ def test_unit_edges(G, d, B):
     _check(EDGES, 2 * G, 2, d, B, 2, False, 40 + G + d + B)
 
 
-# units of work below, at and above 64 and 192 (the whole list in one split)
+# units of work below, at and above 64, 192 and 256 (the whole list in one split)
 @pytest.mark.parametrize("batch,Hkv", [(1, 1), (16, 4), (13, 5), (95, 2), (24, 8), (65, 4)])
 @pytest.mark.parametrize("dense", [False, True])
 def test_split_rule_edges(batch, Hkv, dense):
     print("splits", batch, Hkv, dense, flush=True)
     rng = np.random.default_rng(batch)
     _check(rng.integers(1, 1500, size=batch), 2 * Hkv, Hkv, 64, 64, 2, dense, 90 + batch)
+
+
+# lists over 32 pages with few kv-heads: several rounds of the merge, and lists of
+# several lengths (one page, one round and both sides of it) in rows of one length,
+# also rows that could hold far more (131072 tokens: 2048 pages)
+@pytest.mark.parametrize("lens", [[4500], [70, 1, 64 * 16, 64 * 17, 64 * 64, 64 * 65 + 1]])
+@pytest.mark.parametrize("G,d", [(1, 64), (2, 128), (8, 128)])
+@pytest.mark.parametrize("row", [0, 131072])
+def test_long_lists(lens, G, d, row):
+    print("long lists", lens, G, d, row, flush=True)
+    _check(lens, G, 1, d, 64, 2, True, 120 + len(lens), row)
 
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
