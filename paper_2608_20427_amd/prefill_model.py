@@ -29,62 +29,22 @@ def middle_layers(cfg, count=8):
     return set(range(start, start + count))
 
 
-_JOINT = (("wq", "wk", "wv"), ("wo",), ("wg", "wu"), ("wd",))  # projections of one input
-
-
 class PrefillStack:
     """cfg: a synth.ModelConfig; weights: the generator's bf16 tensors
     (projections stored [in, out]); B, L: block width and local width of the
     BF1 layers.
 
-    On a GPU the projections are copied once into the layout the library GEMMs
-    read best, and ``w`` holds views of that copy: updates of a projection
-    after construction go through ``w``."""
+    ``w`` holds the weights as they were given where they are contiguous tensors
+    of ``device`` already (an update in place is seen by the next call), copies
+    of them otherwise.  (Projections kept joined and transposed would make the
+    GEMMs of 8192 tokens, hidden 1024, 218 us per layer instead of 284, but as a
+    second copy of every projection, which no longer follows the caller's.)"""
 
     def __init__(self, cfg, weights, device="cuda", B=64, L=2):
         self.cfg, self.B, self.L = cfg, B, L
         self.w = {k: v.to(device).contiguous() for k, v in weights.items()}
         self.device = device
         self._rope_n = -1
-        self._joint = {}
-        for l in range(cfg.layers):
-            for names in _JOINT:
-                self._join([f"{l}.{x}" for x in names])
-
-    # Projections that share an input are one [out, in] matrix, their entries of
-    # w the transposed row ranges of it: one GEMM instead of three (or two), and
-    # with the contraction contiguous in both operands.  Measured at 8192 tokens,
-    # hidden 1024 (library GEMM, us): Q, K, V 79 separate, 65 joined, 57 joined
-    # and transposed; gate and up 118, 95, 83; output 37 -> 33 and down 50 -> 45
-    # from the transposed form alone.  Each GEMM also costs 18 us of host time,
-    # which bounds prefills below some 2K tokens.
-    def _join(self, keys):
-        ts = [self.w.get(k) for k in keys]
-        if any(t is None or type(t) is not torch.Tensor or not t.is_cuda or t.dim() != 2 or t.requires_grad
-               or t.dtype != torch.bfloat16 or t.shape[0] != ts[0].shape[0] for t in ts):
-            return
-        m = torch.cat([t.t() for t in ts])
-        self._joint[keys[0]] = m
-        at = 0
-        for k, t in zip(keys, ts):
-            self.w[k] = m[at:at + t.shape[1]].t()
-            at += t.shape[1]
-
-    def _project(self, a, keys):
-        """a @ w[k] for each key: one GEMM while the entries are the adjacent
-        views they were made as, else (an entry was replaced) one each."""
-        w, m = self.w, self._joint.get(keys[0])
-        if m is not None:
-            at, size = m.data_ptr(), m.shape[1] * m.element_size()
-            for k in keys:
-                t = w[k]
-                if t.data_ptr() != at or t.stride() != (1, m.shape[1]) or t.shape[0] != m.shape[1]:
-                    break
-                at += t.shape[1] * size
-            else:
-                if at == m.data_ptr() + m.shape[0] * size:
-                    return (a @ m.t()).split([w[k].shape[1] for k in keys], dim=1)
-        return [a @ w[k] for k in keys]
 
     def _rope_tables(self, n):
         if n != self._rope_n:
@@ -174,6 +134,20 @@ class PrefillStack:
         _check(load().bf1_stack_rms(_ptr(h), _ptr(r), _ptr(gain), _ptr(out), h.shape[0], h.shape[1], self.cfg.eps,
                                     _stream(None, h.device)), "bf1_stack_rms")
         return out
+
+    # Three GEMMs of one input cost 18 us of host time each, which bounds prefills
+    # below some 2K tokens; putting small matrices side by side first costs one
+    # launch and a copy.  Per layer, hidden 1024 (4.2M and 6.3M entries), us,
+    # separate / side by side: 128 to 2048 tokens 187 / 159, 8192 tokens 428 / 409,
+    # 16384 724 / 729; hidden 4096 (16.8M and 100M entries) 128 tokens 309 / 421, 8192
+    # tokens 2458 / 2605.
+    def _project(self, a, keys):
+        """a @ w[k] for each key: one GEMM on the matrices side by side while they
+        are small."""
+        ts = [self.w[k] for k in keys]
+        if sum(t.numel() for t in ts) > 8 << 20:
+            return [a @ t for t in ts]
+        return (a @ torch.cat(ts, 1)).split([t.shape[1] for t in ts], dim=1)
 
     def _layer_fused(self, l, h, r, cos, sin, bf1_layers, dense_attention):
         """One layer between library GEMMs on the row kernels; h is updated in

@@ -176,24 +176,47 @@ def test_dense_attention_callable_sees_contiguous_heads():
     assert torch.equal(a, st.last_logits(ids, {1}))
 
 
-def test_joined_projections_follow_w():
-    # the joined matrices are only a layout of w: an update in place is seen,
-    # a replaced entry is used as it is, and the values are those given
-    ids = torch.from_numpy(synth.make_tokens(CFG, 90, 4)).cuda()
-    given = synth.make_model_weights(CFG, 11)
+@pytest.mark.parametrize("hidden,inter,joined", [(256, 512, True), (1024, 4096, True), (1024, 4104, False)])
+def test_projections_side_by_side(hidden, inter, joined):
+    # up to 2^23 entries one GEMM (rows of all matrices), above one each; a product
+    # of bf16 with fp32 sums of 1024 terms, rounded once (2^-8, and 2^-16 of the
+    # terms' magnitudes for the sums)
+    g = _g(hidden + inter)
     st = _stack()
-    assert all(torch.equal(st.w[k].cpu(), given[k]) for k in given)
+    st.w["0.wg"], st.w["0.wu"] = _n(g, hidden, inter), _n(g, hidden, inter)
+    a = _n(g, 33, hidden)
+    got = st._project(a, ("0.wg", "0.wu"))
+    assert [t.stride() for t in got] == [(2 * inter if joined else inter, 1)] * 2
+    for t, k in zip(got, ("0.wg", "0.wu")):
+        ref, mag = a.double() @ st.w[k].double(), a.double().abs() @ st.w[k].double().abs()
+        assert ((t.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2.0 ** -16 * mag).all()
+
+
+def test_weights_are_the_callers():
+    # contiguous weights on the device are shared, not copied: an update in place
+    # of what the caller passed reaches the next call (bitwise a stack built from
+    # the changed values), two layers may be one tensor, and a replaced entry is
+    # used.  The updates change the result visibly: a norm follows Q and K, so V,
+    # gate and up are the projections changed.
+    ids = torch.from_numpy(synth.make_tokens(CFG, 90, 4)).cuda()
+    given = {k: v.cuda() for k, v in synth.make_model_weights(CFG, 11).items()}
+    for x in ("wq", "wk", "wv", "wo", "wg", "wu", "wd"):
+        given[f"2.{x}"] = given[f"1.{x}"]
+    before = torch.cuda.memory_allocated()
+    st = PrefillStack(CFG, given, device="cuda")
+    assert torch.cuda.memory_allocated() == before
+    assert all(st.w[k].data_ptr() == given[k].data_ptr() and st.w[k].is_contiguous() for k in given)
     base = st.last_logits(ids, {0})
-    st.w["1.wk"].mul_(2)          # in place, inside the joined matrix
-    twice = st.last_logits(ids, {0})
-    other = _stack(**{"1.wk": lambda t: (t * 2).contiguous()})  # its own matrix now
-    a = torch.zeros((4, CFG.hidden), dtype=torch.bfloat16, device="cuda")
-    assert len(other._project(a, ("1.wq", "1.wk", "1.wv"))) == 3
     top = base.abs().max()
-    assert (twice - other.last_logits(ids, {0})).abs().max() <= 2e-2 * top
-    swapped = _stack()
-    swapped.w["0.wg"], swapped.w["0.wu"] = swapped.w["0.wu"], swapped.w["0.wg"]
-    plain = _stack()
-    plain.w["0.wg"], plain.w["0.wu"] = plain.w["0.wu"], plain.w["0.wg"]
-    plain._fused = lambda *x: False
-    assert (swapped.last_logits(ids, {0}) - plain.last_logits(ids, {0})).abs().max() <= 2e-2 * top
+    for change in ("1.wv", "0.wg", "0.wu"):
+        last = st.last_logits(ids, {0})
+        given[change].neg_()
+        now = st.last_logits(ids, {0})
+        assert (now - last).abs().max() > 0.1 * top
+        assert torch.equal(now, PrefillStack(CFG, {k: v.clone() for k, v in given.items()}).last_logits(ids, {0}))
+    last = st.last_logits(ids, {0})
+    st.w["0.wv"] = -st.w["0.wv"]
+    assert (st.last_logits(ids, {0}) - last).abs().max() > 0.1 * top
+    # host weights are copied, on the device and contiguous as well
+    host = PrefillStack(CFG, synth.make_model_weights(CFG, 11), device="cuda")
+    assert all(t.is_cuda and t.is_contiguous() for t in host.w.values())
