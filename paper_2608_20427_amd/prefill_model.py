@@ -89,7 +89,12 @@ class PrefillStack:
         K = k.transpose(0, 1).contiguous().unsqueeze(0)
         V = v.transpose(0, 1).contiguous().unsqueeze(0)
         O = self._attention(l, Q, K, V, bf1_layers, dense_attention)
-        h = h + O[0].transpose(0, 1).reshape(n, H * d) @ w[p + "wo"]
+        return self._tail_plain(l, h, O[0].transpose(0, 1).reshape(n, H * d))
+
+    def _tail_plain(self, l, h, O):
+        """A layer after its attention output O [n, heads * d]."""
+        w, p = self.w, f"{l}."
+        h = h + O @ w[p + "wo"]
         a = self._rms(h, w[p + "post_norm"])
         return h + (torch.nn.functional.silu(a @ w[p + "wg"]) * (a @ w[p + "wu"])) @ w[p + "wd"]
 
@@ -152,7 +157,9 @@ class PrefillStack:
     def _layer_fused(self, l, h, r, cos, sin, bf1_layers, dense_attention):
         """One layer between library GEMMs on the row kernels; h is updated in
         place.  r is the previous layer's MLP output (None before the first),
-        not yet added to h; returns this layer's."""
+        not yet added to h; returns h and this layer's r.  An attention callable
+        may return what the kernels must not take by its pointer, such as a tensor
+        with a gradient: the layer then ends operator by operator."""
         cfg, w, p, lib = self.cfg, self.w, f"{l}.", load()
         n, H, Hkv, d = h.shape[0], cfg.heads, cfg.kv_heads, cfg.head_dim
         a = self._rms_fused(h, r, w[p + "in_norm"])
@@ -163,6 +170,9 @@ class PrefillStack:
                                    _ptr(K), _ptr(V), n, H, Hkv, d, cfg.eps, _stream(None, h.device)), "bf1_stack_heads")
         if l not in bf1_layers and dense_attention is not None:
             O = dense_attention(Q, K, V)[0].transpose(0, 1).reshape(n, H * d)
+            if type(O) is not torch.Tensor or O.dtype != torch.bfloat16 or O.device != h.device \
+                    or (O.requires_grad and torch.is_grad_enabled()):
+                return self._tail_plain(l, h, O), None
         else:
             O = torch.empty((n, H * d), dtype=h.dtype, device=h.device)
             _check(lib.bf1_attn_fwd_token_major(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), 1, n, H, Hkv, d, int(self.B),
@@ -173,7 +183,7 @@ class PrefillStack:
         s = torch.empty(g.shape, dtype=g.dtype, device=g.device)
         _check(lib.bf1_stack_swiglu(_ptr(g), _ptr(u), g.stride(0), u.stride(0), _ptr(s), n, g.shape[1],
                                     _stream(None, h.device)), "bf1_stack_swiglu")
-        return s @ w[p + "wd"]
+        return h, s @ w[p + "wd"]
 
     def last_logits(self, ids, bf1_layers, dense_attention=None):
         """Logits (float32, [vocab]) of the last position after the prefill of
@@ -187,7 +197,7 @@ class PrefillStack:
         with torch.cuda.device(h.device) if h.is_cuda else contextlib.nullcontext():
             for l in range(cfg.layers):
                 if self._fused(l, h, cos):
-                    r = self._layer_fused(l, h, r, cos, sin, bf1_layers, dense_attention)
+                    h, r = self._layer_fused(l, h, r, cos, sin, bf1_layers, dense_attention)
                     continue
                 h, r = h if r is None else h + r, None
                 h = self._layer_plain(l, h, cos, sin, bf1_layers, dense_attention)

@@ -163,6 +163,36 @@ def test_autograd_keeps_the_operators():
     assert st.w["2.wd"].grad is not None and torch.isfinite(st.w["2.wd"].grad).all()
 
 
+def _soft(Q, K, V):
+    # dense causal attention by plain operators, in fp32, for a callable
+    G, n = Q.shape[1] // K.shape[1], Q.shape[2]
+    Q, K, V = Q.float(), K.float().repeat_interleave(G, 1), V.float().repeat_interleave(G, 1)
+    s = Q @ K.transpose(2, 3).contiguous() / Q.shape[-1] ** 0.5
+    s = s.masked_fill(torch.ones(n, n, device=Q.device).triu(1).bool(), float("-inf"))
+    return (s.softmax(-1) @ V).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("leaf", ["scale", "scale and final_norm"])
+def test_gradients_through_the_attention_callable(leaf):
+    # a callable with a parameter of its own: the logits carry its gradient as
+    # they do operator by operator, whatever else wants one.  bf16 gradients of
+    # three layers, a few roundings (2^-8) each, summed over a thousand entries of
+    # both signs.
+    ids = torch.from_numpy(synth.make_tokens(CFG, 70, 4)).cuda()
+    grads = []
+    for plain in (False, True):
+        st = _stack()
+        if leaf != "scale":
+            st.w["final_norm"].requires_grad_()
+        if plain:
+            st._fused = lambda *a: False
+        scale = torch.ones(64, device="cuda", requires_grad=True)
+        out = st.last_logits(ids, {0}, lambda Q, K, V: (_soft(Q, K, V) * scale).to(torch.bfloat16))
+        out.square().sum().backward()
+        grads.append(scale.grad)
+    assert (grads[0] - grads[1]).abs().max() <= 5e-2 * grads[1].abs().max() and grads[1].abs().max() > 0
+
+
 def test_dense_attention_callable_sees_contiguous_heads():
     st = _stack()
     ids = torch.from_numpy(synth.make_tokens(CFG, 200, 4)).cuda()
