@@ -100,12 +100,14 @@ class PrefillStack:
 
     def _fused(self, l, h, cos):
         """Whether layer l can run on the row kernels: bf16 weights of matching
-        shapes on h's GPU, the kernels' head sizes and widths, and no autograd
-        graph wanted through the layer."""
+        shapes on h's GPU, the kernels' head sizes and widths, GEMMs that give bf16,
+        and no autograd graph wanted through the layer."""
         cfg, w, p = self.cfg, self.w, f"{l}."
         if type(h) is not torch.Tensor or not h.is_cuda or h.dtype != torch.bfloat16 or h.dim() != 2 \
                 or cos.device != h.device:
             return False
+        if torch.is_autocast_enabled("cuda") and torch.get_autocast_dtype("cuda") != torch.bfloat16:
+            return False  # the GEMMs' results would not be bf16
         n, hidden = h.shape
         H, Hkv, d = cfg.heads, cfg.kv_heads, cfg.head_dim
         if n == 0 or d not in (64, 128) or hidden % 8 or hidden > 4096 or max(H, Hkv) > 4096:

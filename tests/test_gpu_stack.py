@@ -193,6 +193,26 @@ def test_gradients_through_the_attention_callable(leaf):
     assert (grads[0] - grads[1]).abs().max() <= 5e-2 * grads[1].abs().max() and grads[1].abs().max() > 0
 
 
+def test_autocast_to_another_type_keeps_the_operators():
+    # projections under fp16 autocast are fp16: the attention entry refuses such
+    # V, a callable gets them; under bf16 autocast nothing changes
+    st = _stack()
+    ids = torch.from_numpy(synth.make_tokens(CFG, 70, 4)).cuda()
+    base, seen = st.last_logits(ids, {0}), []
+    with torch.autocast("cuda", dtype=torch.float16):
+        with pytest.raises(ValueError, match="dtype"):
+            st.last_logits(ids, {0, 1, 2})
+
+        def dense(Q, K, V):
+            seen.append(V.dtype)
+            return bf1.dense_causal_fwd(Q, K, V.to(torch.bfloat16), want_lse=False)[0]
+        a = st.last_logits(ids, set(), dense)
+    assert seen == [torch.float16] * 3
+    assert (a - st.last_logits(ids, set())).abs().max() <= 2e-2 * base.abs().max()
+    with torch.autocast("cuda", dtype=torch.bfloat16):
+        assert torch.equal(st.last_logits(ids, {0}), base)
+
+
 def test_dense_attention_callable_sees_contiguous_heads():
     st = _stack()
     ids = torch.from_numpy(synth.make_tokens(CFG, 200, 4)).cuda()
