@@ -16,6 +16,8 @@ weights of the published shapes (timing does not depend on their values).
 import contextlib
 
 import torch
+from torch.autograd import forward_ad
+from torch.utils._device import DeviceContext
 
 from . import _check, _ptr, _stream, attn_fwd, dense_causal_fwd, load
 
@@ -27,6 +29,17 @@ def middle_layers(cfg, count=8):
     eight middle layers of 28, §4.4; here layers 10..17)."""
     start = (cfg.layers - count) // 2
     return set(range(start, start + count))
+
+
+def _operators_followed():
+    """Whether something follows the operators of a call themselves (tracing,
+    compilation, function transforms, forward-mode derivatives, torch's operator
+    modes), to which a kernel launched by pointers would be invisible."""
+    modes = torch.overrides._get_current_function_mode_stack()
+    return (torch.compiler.is_compiling() or torch._C._get_tracing_state() is not None
+            or torch._C._functorch.peek_interpreter_stack() is not None or forward_ad._current_level >= 0
+            or torch._C._len_torch_dispatch_stack() > 0 or torch._ops._len_torch_dispatch_stack_pre_dispatch() > 0
+            or any(not isinstance(m, DeviceContext) for m in modes))
 
 
 class PrefillStack:
@@ -101,13 +114,16 @@ class PrefillStack:
     def _fused(self, l, h, cos):
         """Whether layer l can run on the row kernels: bf16 weights of matching
         shapes on h's GPU, the kernels' head sizes and widths, GEMMs that give bf16,
-        and no autograd graph wanted through the layer."""
+        no autograd graph wanted through the layer and nothing else that follows
+        its operators."""
         cfg, w, p = self.cfg, self.w, f"{l}."
         if type(h) is not torch.Tensor or not h.is_cuda or h.dtype != torch.bfloat16 or h.dim() != 2 \
                 or cos.device != h.device:
             return False
         if torch.is_autocast_enabled("cuda") and torch.get_autocast_dtype("cuda") != torch.bfloat16:
             return False  # the GEMMs' results would not be bf16
+        if _operators_followed():
+            return False
         n, hidden = h.shape
         H, Hkv, d = cfg.heads, cfg.kv_heads, cfg.head_dim
         if n == 0 or d not in (64, 128) or hidden % 8 or hidden > 4096 or max(H, Hkv) > 4096:
@@ -115,25 +131,26 @@ class PrefillStack:
         inter = w[p + "wg"].shape[-1]
         if inter % 8:
             return False
-        grad = torch.is_grad_enabled()
-        if grad and h.requires_grad:
+        if h.requires_grad and torch.is_grad_enabled():
             return False
-        dev = h.device
         for name, shape in (("in_norm", (hidden,)), ("q_norm", (d,)), ("k_norm", (d,)), ("post_norm", (hidden,)),
                             ("wq", (hidden, H * d)), ("wk", (hidden, Hkv * d)), ("wv", (hidden, Hkv * d)),
                             ("wo", (H * d, hidden)), ("wg", (hidden, inter)), ("wu", (hidden, inter)),
                             ("wd", (inter, hidden))):
             t = w[p + name]
-            if t.shape != shape or t.dtype != torch.bfloat16 or t.device != dev or (grad and t.requires_grad):
-                return False
-            if len(shape) == 1 and (not t.is_contiguous() or t.data_ptr() % 16):
+            if not self._weight(t, shape, h) or (len(shape) == 1 and not self._gain(t)):
                 return False
         return True
 
-    def _plain_gain(self, t, h):
-        """Whether norm gain t suits the norm kernel for rows of h."""
-        return t.shape == h.shape[1:] and t.dtype == torch.bfloat16 and t.device == h.device and t.is_contiguous() \
-            and t.data_ptr() % 16 == 0 and not (torch.is_grad_enabled() and t.requires_grad)
+    def _weight(self, t, shape, h):
+        """Whether t is a plain bf16 weight of `shape` on h's device that wants no
+        gradient."""
+        return type(t) in (torch.Tensor, torch.nn.Parameter) and t.shape == shape and t.dtype == torch.bfloat16 \
+            and t.device == h.device and not (t.requires_grad and torch.is_grad_enabled())
+
+    def _gain(self, t):
+        """Whether the kernels can read norm gain t by its pointer."""
+        return t.is_contiguous() and t.data_ptr() % 16 == 0 and not t.is_neg()
 
     def _rms_fused(self, h, r, gain):
         """h <- h + r in place (if r is given), then RMSNorm(h) * gain."""
@@ -205,7 +222,7 @@ class PrefillStack:
                 h = self._layer_plain(l, h, cos, sin, bf1_layers, dense_attention)
             last = h[-1:]
             gain = w["final_norm"]
-            if r is not None and self._plain_gain(gain, h):
+            if r is not None and self._weight(gain, h.shape[1:], h) and self._gain(gain):
                 last = self._rms_fused(last, r[-1:], gain)  # h's last row is not read again
             else:
                 last = self._rms(last if r is None else last + r[-1:], gain)

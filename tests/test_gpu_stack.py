@@ -165,7 +165,7 @@ def test_autograd_keeps_the_operators():
 
 def _soft(Q, K, V):
     # dense causal attention by plain operators, in fp32, for a callable
-    G, n = Q.shape[1] // K.shape[1], Q.shape[2]
+    G, n = int(Q.shape[1]) // int(K.shape[1]), int(Q.shape[2])
     Q, K, V = Q.float(), K.float().repeat_interleave(G, 1), V.float().repeat_interleave(G, 1)
     s = Q @ K.transpose(2, 3).contiguous() / Q.shape[-1] ** 0.5
     s = s.masked_fill(torch.ones(n, n, device=Q.device).triu(1).bool(), float("-inf"))
@@ -211,6 +211,83 @@ def test_autocast_to_another_type_keeps_the_operators():
     assert (a - st.last_logits(ids, set())).abs().max() <= 2e-2 * base.abs().max()
     with torch.autocast("cuda", dtype=torch.bfloat16):
         assert torch.equal(st.last_logits(ids, {0}), base)
+
+
+def _follow_vmap(st, ids, run):
+    return torch.vmap(run)(torch.stack([ids, ids.flip(0)]))[1]
+
+
+def _follow_jvp(st, ids, run):
+    # tangent of every V projection its own value: the derivative along a scaling
+    keys = [f"{l}.wv" for l in range(CFG.layers)]
+    kept = [st.w[k] for k in keys]
+
+    def f(*ts):
+        st.w.update(zip(keys, ts))
+        return run(ids)
+    out = torch.func.jvp(f, tuple(kept), tuple(kept))[1]
+    st.w.update(zip(keys, kept))
+    return out
+
+
+def _follow_dual(st, ids, run):
+    kept = st.w["0.in_norm"]
+    with torch.autograd.forward_ad.dual_level():
+        st.w["0.in_norm"] = torch.autograd.forward_ad.make_dual(kept, kept.clone())
+        out = torch.autograd.forward_ad.unpack_dual(run(ids)).tangent
+    st.w["0.in_norm"] = kept
+    return torch.zeros_like(run(ids)) if out is None else out
+
+
+def _follow_trace(st, ids, run):
+    from torch.fx.experimental.proxy_tensor import make_fx
+    return make_fx(run)(ids)(ids.flip(0))
+
+
+def _follow_jit(st, ids, run):
+    return torch.jit.trace(run, ids, check_trace=False)(ids.flip(0))
+
+
+def _follow_compile(st, ids, run):
+    return torch.compile(run, backend="eager")(ids)
+
+
+def _follow_mode(st, ids, run):
+    class Count(torch.utils._python_dispatch.TorchDispatchMode):
+        seen = 0
+
+        def __torch_dispatch__(self, f, types, args=(), kwargs=None):
+            Count.seen += f is torch.ops.aten.silu.default
+            return f(*args, **(kwargs or {}))
+    with Count():
+        run(ids)
+    return torch.tensor([float(Count.seen)])
+
+
+@pytest.mark.parametrize("follow", [_follow_vmap, _follow_jvp, _follow_dual, _follow_trace, _follow_jit,
+                                    _follow_compile, _follow_mode], ids=lambda f: f.__name__[8:])
+@pytest.mark.filterwarnings("ignore")
+def test_what_follows_the_operators_sees_them(follow):
+    # transforms, traces and modes over a stack of plain operators (a callable for
+    # every layer) give what they give with the row kernels switched off
+    ids = torch.from_numpy(synth.make_tokens(CFG, 70, 4)).cuda()
+    got = []
+    for plain in (True, False):
+        st = _stack()
+        if plain:
+            st._fused = lambda *a: False
+        with torch.no_grad():
+            st._rope_tables(70)
+            got.append(follow(st, ids, lambda x: st.last_logits(x, set(), _soft)))
+    assert got[0].abs().max() > 0
+    assert (got[0] - got[1]).abs().max() <= 2e-2 * got[0].abs().max()
+
+
+def test_default_device_keeps_the_kernels():
+    st = _stack()
+    h = st.w["embed"][:4].clone()
+    with torch.device("cuda"):
+        assert st._fused(0, h, st._rope_tables(4)[0])
 
 
 def test_dense_attention_callable_sees_contiguous_heads():
