@@ -172,6 +172,18 @@ static void plan_cache_and_capture() {
     CHECK(bf1_attn_bwd(P, P, P, P, P, PF, PF, PF, PF, 1, 30001, 16, 8, 128, 64, 2, P, int64_t(1) << 40,
                        nullptr) == BF1_OK);
     CHECK(g_stub.bwds == 2);
+    // a length's first backward: the forward's two tables, then one allocation and
+    // one copy for all lists and cuts; a later one finds every cut
+    for (long n : {300, 1024, 4096}) {
+        bf1_release_plans();
+        const long m = g_stub.mallocs, c = g_stub.copies;
+        CHECK(bf1_attn_bwd(P, P, P, P, P, PF, PF, PF, PF, 1, n, 16, 8, 128, 64, 2, P, int64_t(1) << 40, nullptr) ==
+              BF1_OK);
+        CHECK(g_stub.mallocs - m == 3 && g_stub.copies - c == 1);
+        CHECK(bf1_attn_bwd(P, P, P, P, P, PF, PF, PF, PF, 4, n, 16, 8, 128, 64, 2, P, int64_t(1) << 40, nullptr) ==
+              BF1_OK);
+        CHECK(g_stub.mallocs - m == 3 && g_stub.copies - c == 1);
+    }
     // the forward that allocates nothing: no allocation, and an oversized
     // table is refused before any call
     const long m1 = g_stub.mallocs;

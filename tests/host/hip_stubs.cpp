@@ -32,6 +32,7 @@ hipError_t hipFree(void* p) {
 }
 hipError_t hipMemcpy(void* dst, const void* src, size_t n, hipMemcpyKind) {
     if (g_stub.fail) return hipErrorInvalidValue;
+    ++g_stub.copies;
     std::memcpy(dst, src, n);
     return hipSuccess;
 }
