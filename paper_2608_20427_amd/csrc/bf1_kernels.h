@@ -124,7 +124,8 @@ BF1_HD int32_t decode_pages_per_split(int32_t npages, int32_t outs, int32_t nspl
 }
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream);
 
-// Largest route table (row_ptr and col_idx entries) bf1_attn_fwd_noalloc accepts.
+// Largest route table (row_ptr and col_idx entries) bf1_attn_fwd_noalloc accepts: a
+// bound of its interface, no such table is made.
 constexpr int64_t kNoallocInts = int64_t(1) << 20;
 
 // Route planner: row_ptr[0..NB], col_idx[0..nnz) on `stream`.

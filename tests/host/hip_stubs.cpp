@@ -86,10 +86,4 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t) {
     g_stub.ppw = a.ppw;
     return hipSuccess;
 }
-hipError_t noalloc_scratch(int32_t** ptr) {
-    if (g_stub.fail) return hipErrorInvalidSymbol;
-    static int32_t table[kNoallocInts];
-    *ptr = table;
-    return hipSuccess;
-}
 }  // namespace bf1

@@ -1,6 +1,6 @@
 """Every instance the C ABI advertises, compared with the fp64 oracle on the
-GPU: forward BF1 (head_dim x group x block width: 16 instances), the dense
-comparator (8), the backward (the 14 with G * B >= 128) and decode (16), each
+GPU: forward BF1 (head_dim x group x block width: 16 instances), the same over
+a caller's table with one and with two key groups (32), the dense comparator (8), the backward (the 14 with G * B >= 128) and decode (16), each
 at batch 2 with a ragged length (n = 5 B + 37: several tiles and a partial
 last block); plus forward cases whose scores reach the hundreds, so that the
 lazily rescaled running maximum moves by more than 2^8 several times per row
@@ -56,6 +56,29 @@ def test_forward_every_instance(cfg):
     TP.compare(o, lse, o_ref, l_ref, tag=f"forward {cfg}")
 
 
+@pytest.mark.parametrize("cfg", GRID, ids=ident)
+def test_table_every_instance(cfg):
+    # the kernel that walks a caller's table takes the planner's rows in the order
+    # in which the closed form gives them, so the results are the same bits; one of
+    # the two against the oracle, in both key-group forms
+    d, G, B = cfg
+    TP.say(f"grid table {cfg}")
+    w = _workload(d, G, B, seed=3050 + d + 10 * G + B)
+    q, k, v = synth.make_qkv(w, device="cuda")
+    o_ref, l_ref = orc.attn_gathered_fp64(synth.to_f64(q), synth.to_f64(k), synth.to_f64(v), B, 2)
+    rp, ci = bf1.plan(w.n, B, 2)
+    try:
+        for mode in (1, 2):
+            bf1.set_forward_key_split(mode)
+            o, lse = bf1.attn_fwd_csr(q, k, v, B, rp, ci)
+            o2, lse2 = bf1.attn_fwd(q, k, v, B=B, L=2)
+            torch.cuda.synchronize()
+            TP.compare(o, lse, o_ref, l_ref, tag=f"table {cfg} mode {mode}")
+            assert torch.equal(o, o2) and torch.equal(lse, lse2), mode
+    finally:
+        bf1.set_forward_key_split(0)
+
+
 @pytest.mark.parametrize("cfg", [(d, G) for d in D for G in GROUPS], ids=lambda c: "d{}_G{}".format(*c))
 def test_dense_every_instance(cfg):
     d, G = cfg
@@ -107,6 +130,9 @@ def test_forward_large_logits(cfg):
     o_ref, l_ref = orc.attn_gathered_fp64(synth.to_f64(q), synth.to_f64(k), synth.to_f64(v), B, 2)
     assert np.abs(l_ref).max() > 200.0
     TP.compare(o, lse, o_ref, l_ref, tag=f"large logits {cfg}")
+    o2, lse2 = bf1.attn_fwd_csr(q, k, v, B, *bf1.plan(w.n, B, 2))
+    torch.cuda.synchronize()
+    assert torch.equal(o, o2) and torch.equal(lse, lse2)
 
 
 def test_dense_large_logits():

@@ -53,6 +53,14 @@ def test_both_paths_against_oracle(cfg):
     bf1.set_forward_key_split(0)
     for mode in (1, 2):
         TP.compare(*outs[mode], o_ref, l_ref, tag=f"key groups mode {mode} {cfg}")
+    # the walk of a caller's table: the same tiles in the same order
+    rp, ci = bf1.plan(w.n, w.b, w.L)
+    for mode in (1, 2, 0):
+        bf1.set_forward_key_split(mode)
+        o, lse = bf1.attn_fwd_csr(q, k, v, w.b, rp, ci)
+        torch.cuda.synchronize()
+        assert torch.equal(o, outs[mode][0]) and torch.equal(lse, outs[mode][1]), mode
+    bf1.set_forward_key_split(0)
     nchunk = max(1, (w.Hq // w.Hkv) * w.b // 128)      # 128-row chunks per query block
     items = -(-w.n // w.b) * w.batch * w.Hkv * nchunk
     tiles = bf1.plan_size(w.n, w.b, w.L)[1] * (w.b // 64) * w.batch * w.Hkv * nchunk

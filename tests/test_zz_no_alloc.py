@@ -1,9 +1,9 @@
 """The forward that allocates nothing (bf1_attn_fwd_noalloc), called through
-the C ABI: its route table lives in the library's fixed scratch array, so
-its output must equal bf1_attn_fwd's bitwise (same planner, same kernel),
-and, like it, the fp64 oracle within the forward's bars.  Two calls in a row,
-the second on a smaller input, so the second runs over the first one's
-leftover table."""
+the C ABI: it walks the route in closed form, so its output must equal, bitwise,
+what the kernel gives over the planner's table (another walk of the same tiles in
+the same order), and bf1_attn_fwd's, and lie within the forward's bars of the
+fp64 oracle.  Two calls in a row, the second on a smaller input of other shapes:
+nothing of the first may reach the second."""
 
 import ctypes
 
@@ -57,6 +57,9 @@ def test_noalloc_matches_cached_plan_forward(first, second):
         o_ref, l_ref = bf1.attn_fwd(q, k, v, B=w.b, L=w.L)
         torch.cuda.synchronize()
         assert torch.equal(o, o_ref) and torch.equal(lse, l_ref), w
+        o_tab, l_tab = bf1.attn_fwd_csr(q, k, v, w.b, *bf1.plan(w.n, w.b, w.L))
+        torch.cuda.synchronize()
+        assert torch.equal(o, o_tab) and torch.equal(lse, l_tab), w
     # the small one against the oracle as well
     w, q, k, v, o, lse = cases[1]
     o64, l64 = orc.attn_gathered_fp64(synth.to_f64(q), synth.to_f64(k), synth.to_f64(v), w.b, w.L)
@@ -73,7 +76,7 @@ def test_noalloc_binding_and_limit():
     o_ref, _ = bf1.attn_fwd(q, k, v, B=64, L=2)
     torch.cuda.synchronize()
     assert torch.equal(o, o_ref)
-    # a route table larger than the scratch array is refused before any work
+    # a route whose table would have more than 2^20 entries is refused before any work
     lib = bf1.load()
     fake = ctypes.c_void_p(1 << 20)
     n_big = 1 << 23                                     # NB = 131072 blocks at B = 64
