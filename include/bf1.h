@@ -153,7 +153,10 @@ int bf1_dense_causal_fwd(const void* Q, const void* K, const void* V, void* O, f
  * Pieces of the whole-model prefill (§4.3, §5.3), used by the decoder stack of
  * the Python package around the library GEMMs.  Activations and gains are
  * bf16, rotary tables fp32, all pointers 16-byte aligned device memory;
- * arithmetic is fp32, rounded to bf16 after each operator named below.
+ * arithmetic is fp32, rounded to bf16 after each operator named below.  Sizes
+ * whose launch would reach 2^32 threads (a wave per row of bf1_stack_rms,
+ * head_dim / 16 threads per head row, one per 8 columns of bf1_stack_swiglu) are
+ * BF1_ERR_UNSUPPORTED.
  *
  * bf1_attn_fwd_token_major: bf1_attn_fwd (dense = 0) or bf1_dense_causal_fwd
  *   (dense = 1; B and L ignored) with O as [batch, n, Hq, head_dim], the

@@ -190,6 +190,9 @@ bool aligned16(const void* p) { return p != nullptr && reinterpret_cast<uintptr_
 
 int status_of(hipError_t e) { return e == hipSuccess ? BF1_OK : BF1_ERR_HIP; }
 
+// A launch has fewer than 2^32 threads.
+bool launchable(int64_t blocks) { return blocks < (int64_t(1) << 32) / ROW_THREADS; }
+
 template <int NC>
 hipError_t launch_rms_nc(void* h, const void* r, const void* gain, void* out, int64_t rows, int32_t cols, float eps,
                          hipStream_t s) {
@@ -211,7 +214,7 @@ extern "C" {
 int bf1_stack_rms(void* h, const void* r, const void* gain, void* out, int64_t rows, int32_t cols, float eps,
                   void* stream) {
     if (rows < 0 || rows >= (int64_t(1) << 32) || cols < 1) return BF1_ERR_INVALID_ARG;
-    if (cols % 8 != 0 || cols > 4096) return BF1_ERR_UNSUPPORTED;
+    if (cols % 8 != 0 || cols > 4096 || !bf1::launchable((rows + 3) / 4)) return BF1_ERR_UNSUPPORTED;
     if (rows == 0) return BF1_OK;
     if (!bf1::aligned16(h) || !bf1::aligned16(gain) || !bf1::aligned16(out) || (r && !bf1::aligned16(r)))
         return BF1_ERR_INVALID_ARG;
@@ -238,7 +241,7 @@ int bf1_stack_heads(const void* q, const void* k, const void* v, int64_t ldq, in
     const int64_t rows = n * (H + 2 * (int64_t)Hkv);
     const int rpb = bf1::ROW_THREADS / (head_dim / 16);
     const int64_t grid = (rows + rpb - 1) / rpb;
-    if (grid > 0x7fffffff) return BF1_ERR_UNSUPPORTED;
+    if (!bf1::launchable(grid)) return BF1_ERR_UNSUPPORTED;
     auto launch = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(bf1::ROW_THREADS), 0, (hipStream_t)stream,
                            (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, ldq, ldk, ldv, (const __bf16*)qgain,
@@ -258,7 +261,7 @@ int bf1_stack_swiglu(const void* g, const void* u, int64_t ldg, int64_t ldu, voi
         return BF1_ERR_INVALID_ARG;
     const int32_t nch = cols / 8;
     const int64_t grid = (rows * nch + bf1::ROW_THREADS - 1) / bf1::ROW_THREADS;
-    if (grid > 0x7fffffff) return BF1_ERR_UNSUPPORTED;
+    if (!bf1::launchable(grid)) return BF1_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(bf1::swiglu_kernel, dim3((unsigned)grid), dim3(bf1::ROW_THREADS), 0, (hipStream_t)stream,
                        (const __bf16*)g, (const __bf16*)u, ldg, ldu, (__bf16*)out, rows, nch);
     return bf1::status_of(hipGetLastError());

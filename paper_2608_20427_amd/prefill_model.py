@@ -35,11 +35,11 @@ def _operators_followed():
     """Whether something follows the operators of a call themselves (tracing,
     compilation, function transforms, forward-mode derivatives, torch's operator
     modes), to which a kernel launched by pointers would be invisible."""
-    modes = torch.overrides._get_current_function_mode_stack()
     return (torch.compiler.is_compiling() or torch._C._get_tracing_state() is not None
             or torch._C._functorch.peek_interpreter_stack() is not None or forward_ad._current_level >= 0
             or torch._C._len_torch_dispatch_stack() > 0 or torch._ops._len_torch_dispatch_stack_pre_dispatch() > 0
-            or any(not isinstance(m, DeviceContext) for m in modes))
+            or (torch._C._len_torch_function_stack() > 0 and any(
+                not isinstance(m, DeviceContext) for m in torch.overrides._get_current_function_mode_stack())))
 
 
 class PrefillStack:
@@ -129,28 +129,27 @@ class PrefillStack:
         if n == 0 or d not in (64, 128) or hidden % 8 or hidden > 4096 or max(H, Hkv) > 4096:
             return False
         inter = w[p + "wg"].shape[-1]
-        if inter % 8:
+        # the kernels' launches: a wave per row, d / 16 lanes per head, a lane per 8 of inter
+        if inter % 8 or n * max(64, (H + 2 * Hkv) * (d // 16), inter // 8) >= 1 << 32:
             return False
-        if h.requires_grad and torch.is_grad_enabled():
+        grad = torch.is_grad_enabled()
+        if grad and h.requires_grad:
             return False
         for name, shape in (("in_norm", (hidden,)), ("q_norm", (d,)), ("k_norm", (d,)), ("post_norm", (hidden,)),
                             ("wq", (hidden, H * d)), ("wk", (hidden, Hkv * d)), ("wv", (hidden, Hkv * d)),
                             ("wo", (H * d, hidden)), ("wg", (hidden, inter)), ("wu", (hidden, inter)),
                             ("wd", (inter, hidden))):
             t = w[p + name]
-            if not self._weight(t, shape, h) or (len(shape) == 1 and not self._gain(t)):
+            if not self._weight(t, shape, h.device, grad):
                 return False
         return True
 
-    def _weight(self, t, shape, h):
-        """Whether t is a plain bf16 weight of `shape` on h's device that wants no
-        gradient."""
-        return type(t) in (torch.Tensor, torch.nn.Parameter) and t.shape == shape and t.dtype == torch.bfloat16 \
-            and t.device == h.device and not (t.requires_grad and torch.is_grad_enabled())
-
-    def _gain(self, t):
-        """Whether the kernels can read norm gain t by its pointer."""
-        return t.is_contiguous() and t.data_ptr() % 16 == 0 and not t.is_neg()
+    def _weight(self, t, shape, device, grad):
+        """Whether t is a plain bf16 weight of `shape` on `device` that wants no
+        gradient, and if it is a norm gain one that can be read by its pointer."""
+        return (type(t) is torch.Tensor or type(t) is torch.nn.Parameter) and t.shape == shape \
+            and t.dtype is torch.bfloat16 and t.device == device and not (grad and t.requires_grad) \
+            and (len(shape) > 1 or (t.is_contiguous() and t.data_ptr() % 16 == 0 and not t.is_neg()))
 
     def _rms_fused(self, h, r, gain):
         """h <- h + r in place (if r is given), then RMSNorm(h) * gain."""
@@ -222,7 +221,7 @@ class PrefillStack:
                 h = self._layer_plain(l, h, cos, sin, bf1_layers, dense_attention)
             last = h[-1:]
             gain = w["final_norm"]
-            if r is not None and self._weight(gain, h.shape[1:], h) and self._gain(gain):
+            if r is not None and self._weight(gain, h.shape[1:], h.device, torch.is_grad_enabled()):
                 last = self._rms_fused(last, r[-1:], gain)  # h's last row is not read again
             else:
                 last = self._rms(last if r is None else last + r[-1:], gain)

@@ -305,6 +305,16 @@ def test_decode_invalid_arguments_rejected_without_device(lib):
     assert attn(wsb=1024) == bf1.BF1_ERR_BUFFER_TOO_SMALL
 
 
+def test_stack_sizes_past_a_launch_are_refused(lib):
+    # 2^32 threads or more: nothing is launched
+    fake, f32 = ctypes.c_void_p(1 << 20), ctypes.c_float(1e-6)
+    assert lib.bf1_stack_rms(fake, None, fake, fake, 1 << 26, 1024, f32, None) == bf1.BF1_ERR_UNSUPPORTED
+    assert lib.bf1_stack_swiglu(fake, fake, 24576, 24576, fake, 1 << 21, 24576, None) == bf1.BF1_ERR_UNSUPPORTED
+    for d, n in ((128, 1 << 22), (64, 1 << 23)):  # 128 head rows of d / 16 threads per token
+        assert lib.bf1_stack_heads(fake, fake, fake, 64 * d, 32 * d, 32 * d, fake, fake, fake, fake, fake, fake, fake, n,
+                                   64, 32, d, f32, None) == bf1.BF1_ERR_UNSUPPORTED
+
+
 def test_key_split_mode_checked(lib):
     assert lib.bf1_set_forward_key_split(3) == bf1.BF1_ERR_INVALID_ARG
     assert lib.bf1_set_forward_key_split(-1) == bf1.BF1_ERR_INVALID_ARG

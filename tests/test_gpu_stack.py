@@ -283,6 +283,15 @@ def test_what_follows_the_operators_sees_them(follow):
     assert (got[0] - got[1]).abs().max() <= 2e-2 * got[0].abs().max()
 
 
+def test_sizes_past_a_launch_run_on_operators():
+    # rows that share their memory stand for a prompt of that length
+    st = _stack()
+    row = st.w["embed"][:1]
+    cos, _ = st._rope_tables(1)
+    assert st._fused(0, row.expand((1 << 26) - 1, -1), cos)
+    assert not st._fused(0, row.expand(1 << 26, -1), cos)
+
+
 def test_default_device_keeps_the_kernels():
     st = _stack()
     h = st.w["embed"][:4].clone()
