@@ -120,16 +120,17 @@ int64_t decode_ws_splits(int64_t batch, int64_t Hkv, int64_t P) {
 // 20.9 / 22.8, 384 28.3 / 27.5 / 30.0, 512 30.7 / 34.4 / 34.0; eight: 256 24.0 / 23.3 /
 // 25.1, 320 27.9 / 28.6 / 29.6.  Below that line two splits from 193 units on, the
 // finest cut before; up to 64 units at most 16 splits, one round of the merge, or
-// where a merge thread has two or more outputs, some four per compute unit.
+// where a merge thread has two or more outputs, one workgroup per compute unit and
+// at least four splits.
 //
 // Longer lists (dense ones) are cut for four workgroups per compute unit into at
 // most 32 splits, or for one per compute unit (two with heads of 64) where that
-// makes more, and above 32 pages into no more rounds than decode_rounds (its
-// comment has the figures; 24 pages of 128 tokens, 10.6 with 24 splits, 11.6 with
-// 12): 16/8 heads of 128, 1024 pages, 4 units 48.0 / 35.0 / 40.5 with 32 / 64 / 128,
-// 8 units 51.8 / 53.3 with 32 / 64, 16 units 92.2 / 88.2 / 93.3 with 16 / 32 / 64; heads of
-// 64, 8 units 39.6 / 33.4 / 40.3 with 32 / 64 / 128.  A list in a row for more than 32
-// pages is cut by its own length (ppw 0, decode_pages_per_split).
+// makes at least 64 and as many merge rounds pay (decode_rounds has the figures):
+// 16/8 heads of 128, 1024 pages, 4 units 48.0 / 35.0 / 40.5 with 32 / 64 / 128, 8 units
+// 51.8 / 53.3 with 32 / 64, 16 units 92.2 / 88.2 / 93.3 with 16 / 32 / 64; heads of 64, 8
+// units 39.6 / 33.4 / 40.3 with 32 / 64 / 128.  The grid has no split that a full list
+// leaves empty: workgroups go to the chiplets in turn, and 20 of 32 in use load
+// them 3 : 2 (40 pages of 128, 12 units, 18.3 us instead of 15.3).
 void decode_splits(int64_t batch, int64_t Hkv, int64_t G, int64_t D, int64_t B, int64_t P, int32_t* nsplit,
                    int32_t* ppw) {
     // by head size, page width and q-heads per kv-head (1, 2, 4, 8)
@@ -139,9 +140,10 @@ void decode_splits(int64_t batch, int64_t Hkv, int64_t G, int64_t D, int64_t B, 
     const int64_t outs = (G * D + 255) / 256;
     int64_t want = (1024 + units - 1) / units;
     if (P > 16) {
+        want = std::min<int64_t>(want, 32);
         const int64_t fill = ((D == 64 ? 512 : 256) + units - 1) / units;
-        want = std::max(std::min<int64_t>(want, 32), fill);
-        if (P > 32) want = std::min<int64_t>(want, 16 * bf1::decode_rounds((int32_t)P, (int32_t)outs, 256));
+        if (fill >= 64)
+            want = std::max(want, std::min<int64_t>(fill, 16 * bf1::decode_rounds(P * B, (int32_t)outs, 256)));
     } else if (units >= uncut_from[D == 128][B == 128][G == 8 ? 3 : G / 2]) {
         want = 1;
     } else if (units > 192) {
@@ -149,8 +151,9 @@ void decode_splits(int64_t batch, int64_t Hkv, int64_t G, int64_t D, int64_t B, 
     } else if (units <= 64) {
         want = outs == 1 ? 16 : std::max<int64_t>(4, (256 + units - 1) / units);
     }
-    *nsplit = (int32_t)std::min(want, decode_ws_splits(batch, Hkv, P));
-    *ppw = P > 32 ? 0 : (int32_t)((P + *nsplit - 1) / *nsplit);
+    const int64_t most = std::min(want, decode_ws_splits(batch, Hkv, P));
+    *ppw = (int32_t)((P + most - 1) / most);
+    *nsplit = (int32_t)((P + *ppw - 1) / *ppw);
 }
 
 int64_t decode_ws_bytes(int64_t batch, int64_t Hq, int64_t Hkv, int64_t D, int64_t nsplit) {

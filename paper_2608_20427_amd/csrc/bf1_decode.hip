@@ -23,7 +23,7 @@
 // before it can address the cache.
 //
 // Split kernel: one workgroup of four waves per (sequence, kv-head, split);
-// a split is `ppw` consecutive pages of the sequence's list (earlier pages,
+// a split is some consecutive pages of the sequence's list (earlier pages,
 // then the self page).  Each wave takes 16 keys of every 64 as one matrix tile
 // and keeps an online softmax (log2 units).  The four waves merge in LDS; a
 // split that covers the whole list writes O and LSE at once, otherwise it
@@ -118,6 +118,10 @@ __global__ __launch_bounds__(PLAN_THREADS) void decode_plan_kernel(
 
 template <int D, int G>
 constexpr int MERGE_OUTS = (G * D + DEC_THREADS - 1) / DEC_THREADS;  // outputs of a merge thread
+
+// Whether a list is cut by its own length instead of its row's: less than half
+// of a row for more than 32 pages (the cut's divisions cost 0.3 us of a step).
+__device__ __forceinline__ bool short_list(int npages, int cap) { return cap >= 32 && 2 * (int64_t)npages <= cap; }
 
 // What one step of sequence b reads: its newest position t, block j and the
 // number c of earlier pages in its plan row.  False if the plan row was made
@@ -263,7 +267,7 @@ __global__ __launch_bounds__(DEC_THREADS, 4) void decode_kernel(
     }
     const int c = sv.c;
     const int npages = c + 1;
-    if (ppw == 0) ppw = decode_pages_per_split(npages, MERGE_OUTS<D, G>, nsplit);
+    if (short_list(npages, cap)) ppw = decode_pages_per_split(npages, PW, MERGE_OUTS<D, G>, nsplit);
     const int nsb = (npages + ppw - 1) / ppw;
     if (s >= nsb) return;
     const int p0 = s * ppw;
@@ -492,7 +496,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_merge_kernel(
     StepView sv;
     if (!step_view(seq_lens, plan + (int64_t)b * stride, cap, PW, b, &sv))
         return;  // the split kernel wrote NaN
-    if (ppw == 0) ppw = decode_pages_per_split(sv.c + 1, MERGE_OUTS<D, G>, nsplit);
+    if (short_list(sv.c + 1, cap)) ppw = decode_pages_per_split(sv.c + 1, PW, MERGE_OUTS<D, G>, nsplit);
     const int nsb = (sv.c + ppw) / ppw;
     if (nsb <= 1) return;  // the split kernel wrote the result
     const float* recs = ws + (int64_t)bh * nsplit * REC;

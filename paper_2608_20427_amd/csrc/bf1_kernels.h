@@ -100,25 +100,25 @@ struct DecodeArgs {
     int32_t head_dim;           // 64 or 128
     int32_t B;                  // 64 or 128
     int32_t nsplit;             // most splits per (sequence, kv-head), <= 256
-    int32_t ppw;                // pages per split; 0: by decode_pages_per_split
+    int32_t ppw;                // pages per split of a list that fills its row
 };
-// How a list of decode pages is cut.  Splits are walked side by side, their
+// How a long list of decode pages is cut.  Splits are walked side by side, their
 // records merged in rounds of 16 loads, for each of `outs` outputs of a merge
-// thread; a page costs about as much as a round (1.1 against 1.3 us).  A list
-// is therefore best cut into 4 sqrt(pages / outs) splits: 1024 pages, one
-// output, 46 us with 32 splits, 31 with 128, 41 with 256; four outputs, 55 with
-// 32, 51 with 64, 69 with 128.  Whole rounds, and never less than one.
-BF1_HD int32_t decode_rounds(int32_t npages, int32_t outs, int32_t nsplit) {
+// thread; 64 keys take some 1.1 us with heads of 128, 0.85 with 64, a round 1.3.  A
+// round more pays while it shortens the longest split by more than it costs:
+// keys / 64 >= 25 r (r + 1) outs for round r + 1.  1024 pages of 64, one output: 46 us
+// with 32 splits, 32 with 64, 31 with 128, 41 with 256; four outputs: 55 with 32, 51
+// with 64, 69 with 128; 256 pages, four outputs: 31 with 16, 29 with 32, 37 with 64.
+BF1_HD int32_t decode_rounds(int64_t keys, int32_t outs, int32_t nsplit) {
     int32_t r = 1;
-    while (16 * r < nsplit && (int64_t)16 * (r + 1) * (r + 1) * outs <= npages) ++r;
+    while (16 * r < nsplit && (int64_t)25 * 64 * r * (r + 1) * outs <= keys) ++r;
     return r;
 }
-// Pages per split of a list cut into at most nsplit.  It is the list's own
-// length that counts, not what its plan row could hold: 128 pages in a row for
-// 2048, 16/8 heads, 77 us at the row's split length, 16 at its own.  (Rows of up
-// to 32 pages keep one length: the two divisions cost 0.3 us of some 9.)
-BF1_HD int32_t decode_pages_per_split(int32_t npages, int32_t outs, int32_t nsplit) {
-    const int32_t r = 16 * decode_rounds(npages, outs, nsplit);
+// Pages per split of a list cut into at most nsplit by its own length, for lists
+// far shorter than their plan row could hold: 128 pages in a row for 2048, 16/8
+// heads, 77 us at the row's split length, 16 at their own.
+BF1_HD int32_t decode_pages_per_split(int32_t npages, int32_t page_keys, int32_t outs, int32_t nsplit) {
+    const int32_t r = 16 * decode_rounds((int64_t)npages * page_keys, outs, nsplit);
     const int32_t most = r < nsplit ? r : nsplit;
     return (npages + most - 1) / most;
 }

@@ -199,12 +199,17 @@ static void plan_cache_and_capture() {
 // Splits of decode steps: the records always fit the workspace, also for lists
 // shorter than their rows could hold; a long list of few kv-heads fills the
 // chip whatever its row could hold; uncut lists where the merge costs more.
-static int64_t per_split(int64_t pages, int32_t outs) {
-    return g_stub.ppw ? g_stub.ppw : bf1::decode_pages_per_split((int32_t)pages, outs, g_stub.nsplit);
+static int64_t g_row = 0;  // pages that the last step's plan row could hold
+static int64_t per_split(int64_t pages, int32_t outs, int32_t B = 64) {
+    // as the kernels choose: a list below half of a long row is cut by its own length
+    if (g_row >= 33 && 2 * pages <= g_row - 1)
+        return bf1::decode_pages_per_split((int32_t)pages, B, outs, g_stub.nsplit);
+    return g_stub.ppw;
 }
 static int32_t splits(int batch, int Hkv, int G, int D, int B, int64_t pages) {
     int32_t* ip = reinterpret_cast<int32_t*>(P);
     int64_t ws = 0;
+    g_row = pages;
     const int32_t stride = (int32_t)pages + 2;
     CHECK(bf1_decode_workspace_size(batch, G * Hkv, Hkv, D, stride, &ws) == BF1_OK);
     CHECK(bf1_decode_attn(P, P, P, ip, 8, ip, stride, P, PF, batch, G * Hkv, Hkv, D, B, P, ws - 1, nullptr) ==
@@ -227,13 +232,17 @@ static void decode_splits() {
                         // lists up to the row's length: every page in a split, never more splits than records
                         for (int64_t m : {int64_t(1), int64_t(2), pages / 7 + 1, pages / 2 + 1, pages}) {
                             if (m > pages) continue;
-                            const int64_t per = per_split(m, outs);
+                            const int64_t per = per_split(m, outs, B);
                             CHECK(per >= 1 && per * most >= m && (m + per - 1) / per <= most);
                         }
                     }
     // one 64K dense list, pages of 64: at most 16 pages in a row on few kv-heads
     for (int units : {1, 2, 4}) CHECK(splits(units, 1, 2, 128, 64, 1024) > 32 && per_split(1024, 1) <= 16);
-    CHECK(splits(1, 1, 8, 128, 64, 1024) > 32 && per_split(1024, 4) <= 16);
+    CHECK(splits(1, 1, 8, 128, 64, 1024) > 32 && per_split(1024, 4) <= 22);
+    // no fewer splits than 32 where the pages are twice as wide (one 30K list, 16/2 heads)
+    CHECK(splits(3, 2, 8, 128, 128, 230) == 29 && per_split(230, 4, 128) == 8);
+    // no split is empty for a full list (40 pages of 128, 12 units)
+    CHECK(splits(6, 2, 1, 128, 128, 40) == 20 && per_split(40, 1, 128) == 2);
     // the same 128 pages in a row that could hold 2048
     for (int units : {1, 2, 8, 32}) CHECK(splits(units, 1, 2, 128, 64, 2048) > 1 && per_split(128, 1) <= 8);
     // selected lists: finest on few units, uncut on many, the line by the instance
